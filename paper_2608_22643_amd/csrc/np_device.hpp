@@ -54,9 +54,12 @@ __device__ inline uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint
 // The same with the nontemporal hint: weight records streamed once per use,
 // which the caches need not keep (measured 3-8% faster for the MLP streams).
 constexpr int CPOL_NT = 2;
+__device__ inline uint4 as_uint4(u32x4_t v) { return make_uint4(v.x, v.y, v.z, v.w); }
+__device__ inline u32x4_t buf_load16v_nt(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, CPOL_NT);
+}
 __device__ inline uint4 buf_load16_nt(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, CPOL_NT);
-  return make_uint4(v.x, v.y, v.z, v.w);
+  return as_uint4(buf_load16v_nt(r, voff, soff));
 }
 
 // Cache policy "sc1" on gfx950: agent (device) scope.  A store with it is
@@ -255,50 +258,81 @@ __device__ inline float group_sum(float v) {
   return v;
 }
 
-// Reduce-scatter of N values (N a power of two, 2 <= N <= 64) over a wave:
-// on entry every lane holds v[0..N-1]; on return lane l holds in v[0] the
-// wave sum of value l / (64/N) (every lane of that group of 64/N lanes holds
-// it).  Each halving step sends the half a lane gives up to its partner, so
-// the N sums cost N - 1 + log2(64/N) shuffles instead of N * 6.  Element
-// indices are template constants throughout, so every access is static and
-// each choice between two halves is one select.
-template <int I, int HALF, int M>
-struct RsStep {
-  template <int N>
-  __device__ static inline void run(float (&v)[N], bool hi) {
-    const float send = hi ? v[I] : v[I + HALF];
-    const float keep = hi ? v[I + HALF] : v[I];
-    v[I] = keep + __shfl_xor(send, M, WAVE);
-    RsStep<I + 1, HALF, M>::run(v, hi);
-  }
-};
-template <int HALF, int M>
-struct RsStep<HALF, HALF, M> {
-  template <int N>
-  __device__ static inline void run(float (&)[N], bool) {}
-};
+// v of the lane that a DPP control names, every lane taking part (the
+// controls used here have a source lane for each lane).
+constexpr int DPP_XOR1 = 0xB1;   // quad_perm [1, 0, 3, 2]: lane ^ 1
+constexpr int DPP_XOR2 = 0x4E;   // quad_perm [2, 3, 0, 1]: lane ^ 2
+constexpr int DPP_XOR3 = 0x1B;   // quad_perm [3, 2, 1, 0]: lane ^ 3
+constexpr int DPP_XOR7 = 0x141;  // row_half_mirror: lane ^ 7
+constexpr int DPP_XOR8 = 0x128;  // row_ror:8: lane ^ 8
 
-template <int CNT, int M>
-struct RsLevel {  // CNT values left, partner distance M
-  template <int N>
-  __device__ static inline void run(float (&v)[N], int lane) {
-    RsStep<0, CNT / 2, M>::run(v, (lane & M) != 0);
-    RsLevel<CNT / 2, M / 2>::run(v, lane);
-  }
-};
-template <int M>
-struct RsLevel<1, M> {  // one value left: sum it over the remaining lanes
-  template <int N>
-  __device__ static inline void run(float (&v)[N], int) {
-#pragma unroll
-    for (int m = M; m >= 1; m >>= 1) v[0] += __shfl_xor(v[0], m, WAVE);
-  }
-};
+template <int CTRL>
+__device__ inline float dpp_f32(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
 
+__device__ inline float dpp_xor4(float v) { return dpp_f32<DPP_XOR3>(dpp_f32<DPP_XOR7>(v)); }
+
+// One exchange across the halves of the wave (or of each 32 lanes): lanes
+// with bit 32 (16) clear return the pair sum of a, the others that of b.
+__device__ inline float swap32_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ inline float swap16_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Sum over the 16 lanes whose numbers agree in their low two bits (a fixed
+// tree); every lane receives it.
+__device__ inline float sum_quads(float v) {
+  v += dpp_xor4(v);
+  v += dpp_f32<DPP_XOR8>(v);
+  v = swap16_add(v, v);
+  return swap32_add(v, v);
+}
+
+// Reduce-scatter of N values (N = 4, 8 or 16) over a wave: on entry every
+// lane holds v[0..N-1]; on return lane l holds in v[0] the wave sum of value
+// l / (64/N) (every lane of that group of 64/N lanes holds it).  Each halving
+// step hands the half a lane gives up to its partner, so the N sums cost
+// N - 1 + log2(64/N) exchanges instead of N * 6, all of them register moves
+// (lane swaps and DPP) with no LDS round trip in the chain.
 template <int N>
 __device__ inline void wave_reduce_scatter(float (&v)[N]) {
-  static_assert(N >= 2 && N <= WAVE && (N & (N - 1)) == 0, "N: power of two in [2, 64]");
-  RsLevel<N, WAVE / 2>::run(v, (int)(threadIdx.x & (WAVE - 1)));
+  static_assert(N == 4 || N == 8 || N == 16, "N: 4, 8 or 16");
+  const int lane = (int)(threadIdx.x & (WAVE - 1));
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) v[i] = swap32_add(v[i], v[i + N / 2]);
+#pragma unroll
+  for (int i = 0; i < N / 4; ++i) v[i] = swap16_add(v[i], v[i + N / 4]);
+  if constexpr (N >= 8) {
+#pragma unroll
+    for (int i = 0; i < N / 8; ++i) {
+      const bool hi = (lane & 8) != 0;
+      const float send = hi ? v[i] : v[i + N / 8], keep = hi ? v[i + N / 8] : v[i];
+      v[i] = keep + dpp_f32<DPP_XOR8>(send);
+    }
+  } else {
+    v[0] += dpp_f32<DPP_XOR8>(v[0]);
+  }
+  if constexpr (N == 16) {
+    const bool hi = (lane & 4) != 0;
+    const float send = hi ? v[0] : v[1], keep = hi ? v[1] : v[0];
+    v[0] = keep + dpp_xor4(send);
+  }
+  v[0] += dpp_f32<DPP_XOR1>(v[0]);
+  v[0] += dpp_f32<DPP_XOR2>(v[0]);
+  if constexpr (N < 16) v[0] += dpp_f32<DPP_XOR7>(v[0]);  // quads hold equal sums: lane ^ 4
+}
+
+// Orders this workgroup's LDS accesses before and after a barrier, and
+// nothing else: unlike __syncthreads() it leaves loads from memory in flight.
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 __device__ inline uint32_t wave_incl_scan(uint32_t v) {

@@ -11,10 +11,13 @@
 // Its waves form `teams` row teams of P waves; each round, team j takes R
 // rows of the range.  Within a team, wave p owns a fixed slice of the d
 // columns (64*CPL 16-byte vectors of each of gate, up and downT), so
-//   * every wave instruction reads 1 KiB of contiguous memory, and all
-//     3*R*CPL loads of a round are issued before any arithmetic;
+//   * every wave instruction reads 1 KiB of contiguous memory, and the loads
+//     run a round ahead: a register of gate or up takes the next round's row
+//     as soon as this round's dot product has used it, one of downT as soon
+//     as its row is accumulated, so the stream never drains between rounds;
 //   * the gate/up dot products of a row are P per-wave partial sums that
-//     meet through a few bytes of LDS (fixed order);
+//     meet through a few bytes of LDS (fixed order), behind a barrier that
+//     waits for LDS only and leaves the record loads in flight;
 //   * the wave's share of y (its column slice) stays in registers; the teams'
 //     partial y meet once in LDS at the end (fixed order) and team 0 writes
 //     the workgroup's partial y to the workspace.
@@ -48,7 +51,7 @@ struct MlpArgs {
   const uint4* x;
   float* partials;         // [d/16][n_wg][16] fp32
   void* ws;
-  int n_active, C, NV, n_wg, P, PP, teams;  // PP: P rounded up to a power of two
+  int n_active, C, NV, n_wg, P, teams;
   uint32_t layer_bytes;  // resident bytes of the layer (< 2^31)
   void* y;               // single-kernel path: the output
   const int32_t* n_dev;  // nullptr, or the row count at n_dev[layer] (<= n_active)
@@ -81,6 +84,10 @@ __device__ inline int row_slot(const MlpArgs& a, int r, int b) {
 // the waves in order).  The barrier's spin is bounded (polls of about 1 us
 // each).
 constexpr uint32_t MLP_SPIN_LIMIT = 1u << 20;
+
+// Rows of the active list one workgroup takes at most (their slots are in its
+// LDS; the launcher gives at least n / MLP_WG_ROWS workgroups: 128 at most).
+constexpr int MLP_WG_ROWS = 512;
 
 template <class T>
 __device__ inline void store_y4(void* y, int col, float4 v) {
@@ -159,13 +166,7 @@ __device__ inline void fused_reduce(const MlpArgs& a, int gen0, float4* red) {
         acc.w += v[h].w;
       }
     }
-#pragma unroll
-    for (int m = 4; m < WAVE; m <<= 1) {
-      acc.x += __shfl_xor(acc.x, m, WAVE);
-      acc.y += __shfl_xor(acc.y, m, WAVE);
-      acc.z += __shfl_xor(acc.z, m, WAVE);
-      acc.w += __shfl_xor(acc.w, m, WAVE);
-    }
+    acc = make_float4(sum_quads(acc.x), sum_quads(acc.y), sum_quads(acc.z), sum_quads(acc.w));
     if (lane < 4) red[w * 4 + lane] = acc;
     __syncthreads();
     if (t < 4 && cok) {  // waves in order
@@ -182,18 +183,25 @@ __device__ inline void fused_reduce(const MlpArgs& a, int gen0, float4* red) {
   }
 }
 
+// HBM-bound: 2 flops per weight byte.  What a shape takes is the record
+// stream, the launch (about 2 us), the dependent slot load at entry (0.9 us)
+// and the partials written at the end.  Loading a round only once the last
+// one was done (8-row rounds, all loads before any arithmetic) left the
+// stream idle during each round's exchange and sums: the rows kernel alone
+// took 51.8 us on a dense 270 MB layer and 25.0 us on 115 MB of active rows;
+// with the registers refilled as they are used, in 4-row rounds, it takes
+// 41.9 us (6.45 TB/s, a plain read of the same records 40.6) and 21.2 us
+// (plain read 19.0).  R = 2, 3, 5, 6 and 8 measured 0-15% slower than 4.
 template <class T, int CPL, int R, int MAXT, bool FUSED>
 __global__ __launch_bounds__(MAXT) void sparse_mlp_rows_kernel(MlpArgs a) {
   constexpr int V = T::V;
-  // a round's R rows are finished in S stages of RS rows: the gate/up sums of
-  // stage s are reduced, exchanged and applied while later stages' records
-  // are still arriving (four stages for 8 rows over 9-10 waves, whose
-  // exchange holds 2 * RS values of 16 lanes each in one wave)
-  constexpr int S = (R >= 8 && MAXT > 512) ? 4 : (R >= 4 ? 2 : 1);
-  constexpr int RS = R / S;
-  constexpr int NVAL = 2 * RS;        // g and u of each stage row
-  constexpr int G = WAVE / NVAL;      // lanes holding one reduced value
-  __shared__ float gu[S][4][NVAL][16];  // stage, team, value, wave
+  constexpr int NVAL = 2 * R;           // g and u of each row of a round
+  constexpr int G = WAVE / NVAL;        // lanes holding one reduced value
+  constexpr int MAXW = MAXT / WAVE;     // waves of a workgroup
+  // round parity (a wave may write the next round's sums while another still
+  // reads this round's), wave, value
+  __shared__ float gu[2][MAXW][NVAL];
+  __shared__ int slot_s[MLP_WG_ROWS];    // the slots of the workgroup's rows, -1 if none
   extern __shared__ float4 team_part[];  // (teams - 1) partial y of d floats
   const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
   const int P = a.P, teams = a.teams;
@@ -222,19 +230,30 @@ __global__ __launch_bounds__(MAXT) void sparse_mlp_rows_kernel(MlpArgs a) {
     gen0 = __hip_atomic_load((int*)((char*)a.ws + WS_BAR_GEN), __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
 
-  // first round's slots (lane r: row r) and x, both in flight before the
-  // first wait
-  int my_slot = -1;
-  {
-    const int r0 = row_begin + team * R;
-    if (lane < R && r0 + lane < row_end) my_slot = row_slot(a, r0 + lane, b);
-  }
-  // Loads below are unconditional, with no branches around them, so the
-  // compiler can wait for each stage's loads alone.  Record loads are buffer
-  // loads: lanes past the slice and rows without a valid slot use an
-  // out-of-range offset and read zeros without touching memory.
+  // The first round's slots (lane r: row r of the team) come straight from
+  // the list; the whole range goes to LDS behind them, so that the rounds
+  // read their slots without a memory access queued behind the records.  -1:
+  // past the range, or a row without a resident slot, which is reported.
+  const bool in0 = lane < R && row_begin + team * R + lane < row_end;
+  const int raw0 = in0 ? row_slot(a, row_begin + team * R + lane, b) : -1;
+  const int nrows = row_end - row_begin;
+  const bool fill = !dense && (int)threadIdx.x < nrows;
+  auto checked = [&](int slot) {
+    if (slot >= 0 && slot < a.C) return slot;
+    raise_error(a.ws, NP_DEVERR_NOT_RESIDENT);
+    return -1;
+  };
+  const int rawf = fill ? row_slot(a, row_begin + threadIdx.x, b) : 0;
+  // Record loads are buffer loads with no branches around them: lanes past
+  // the column slice and rows without a slot use an out-of-range offset and
+  // read zeros without touching memory.
   const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(a.res_layer, a.layer_bytes);
   const uint32_t third = (uint32_t)a.NV * 16u;
+  auto row_off = [&](int slots, int r) {
+    const int slot = __builtin_amdgcn_readlane(slots, r);
+    return slot >= 0 ? (uint32_t)slot * 3u * third : BUF_OOB;
+  };
+  int cur = raw0 >= 0 && raw0 < a.C ? raw0 : -1;
   uint4 xr[CPL];
   bool vok[CPL];
   uint32_t loff[CPL];  // this lane's byte offset within a third of a record
@@ -245,94 +264,116 @@ __global__ __launch_bounds__(MAXT) void sparse_mlp_rows_kernel(MlpArgs a) {
     loff[c] = vok[c] ? (uint32_t)v * 16u : BUF_OOB;
     xr[c] = a.x[vok[c] ? v : 0];
   }
+  __builtin_amdgcn_sched_barrier(0);
+  // the first round's records (offsets: both terms < 2^31, no wrap)
+  u32x4_t gw[R][CPL], uw[R][CPL], dw[R][CPL];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t roff = row_off(cur, r);
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+      gw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], 0);
+      uw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], third);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t roff = row_off(cur, r);
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) dw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], 2 * third);
+  }
+  if (!dense) {
+    if (fill) slot_s[threadIdx.x] = checked(rawf);
+    for (int i = threadIdx.x + blockDim.x; i < nrows; i += blockDim.x)
+      slot_s[i] = checked(row_slot(a, row_begin + i, b));
+    lds_barrier();
+  }
+  auto round_slots = [&](int rb) {
+    const int row = rb + team * R + lane;
+    if (lane >= R || row >= row_end) return -1;
+    return dense ? row_slot(a, row, b) : slot_s[row - row_begin];
+  };
+  int nxt = round_slots(row_begin + teams * R);
   float yacc[CPL][V];
 #pragma unroll
   for (int c = 0; c < CPL; ++c)
 #pragma unroll
     for (int e = 0; e < V; ++e) yacc[c][e] = 0.f;
 
-  // every wave runs the same number of rounds (barriers inside)
-  for (int rb = row_begin; rb < row_end; rb += teams * R) {
-    const int r0 = rb + team * R;
-    int slot[R];
-    bool valid[R];
-    bool bad = false;  // a row of the active list without a resident slot
+  // every wave runs the same number of rounds (a barrier inside)
+  int par = 0;
+  for (int rb = row_begin; rb < row_end; rb += teams * R, par ^= 1) {
+    const int nxt2 = round_slots(rb + 2 * teams * R);  // the round after the next
+    float v[NVAL];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      slot[r] = __builtin_amdgcn_readlane(my_slot, r);
-      valid[r] = r0 + r < row_end && slot[r] >= 0 && slot[r] < a.C;
-      bad |= r0 + r < row_end && !valid[r];
-    }
-    if (bad && threadIdx.x == 0) raise_error(a.ws, NP_DEVERR_NOT_RESIDENT);
-    // all records of the round, in row order
-    uint4 gw[R][CPL], uw[R][CPL], dw[R][CPL];
+      float g = 0.f, u = 0.f;
+      const uint32_t roff = row_off(nxt, r);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const uint32_t roff = valid[r] ? (uint32_t)slot[r] * 3u * third : BUF_OOB;
+      for (int c = 0; c < CPL; ++c) {  // lanes past the slice hold zeros
+        g = T::dot(as_uint4(gw[r][c]), xr[c], g);
+        u = T::dot(as_uint4(uw[r][c]), xr[c], u);
+      }
+      // the refill stays behind the last use of its registers (moved ahead
+      // of it, it would take registers of its own and a copy at the end of
+      // the round that waits for every load): the empty statement uses the
+      // sums, and neither it nor a load moves over the scheduling barrier
+      asm volatile("" : "+v"(g), "+v"(u));
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int c = 0; c < CPL; ++c) {
-        const uint32_t off = roff + loff[c];  // both < 2^31: no wrap
-        gw[r][c] = buf_load16_nt(rsrc, off, 0);
-        uw[r][c] = buf_load16_nt(rsrc, off, third);
-        dw[r][c] = buf_load16_nt(rsrc, off, 2 * third);
+        gw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], 0);
+        uw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], third);
       }
+      v[r] = g;
+      v[R + r] = u;
     }
-    // next round's slots, in flight behind this round's records
-    {
-      const int rn = r0 + teams * R;
-      my_slot = (lane < R && rn + lane < row_end) ? row_slot(a, rn + lane, b) : -1;
+    __builtin_amdgcn_sched_barrier(0);
+    wave_reduce_scatter<NVAL>(v);  // lane l holds the wave sum of value l / G
+    float t = v[0];
+    if (P > 1) {
+      // the P waves' sums of each value meet in LDS: lane NVAL*q + i reads
+      // value i of waves q, q + G, ..., and a fixed tree over the lanes of
+      // a value adds them
+      if (lane % G == 0) gu[par][wid][lane / G] = t;
+      lds_barrier();
+      const int val = lane % NVAL;
+      t = 0.f;
+      for (int q = lane / NVAL; q < P; q += G) t += gu[par][team * P + q][val];
+      if constexpr (NVAL <= 4) t += dpp_xor4(t);
+      if constexpr (NVAL <= 8) t += dpp_f32<DPP_XOR8>(t);
+      t = swap16_add(t, t);
+      t = swap32_add(t, t);
+    }
+    float act[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      // value i sits in lane i after the exchange, in lanes i*G.. without it
+      const int lg = P > 1 ? r : r * G, lu = P > 1 ? R + r : (R + r) * G;
+      const float gs = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), lg));
+      const float us = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), lu));
+      act[r] = gated(a.act, gs, us);
+      // a row without a slot adds nothing, whatever x holds
+      if (fabsf(act[r]) < thr || __builtin_amdgcn_readlane(cur, r) < 0) act[r] = 0.f;
     }
 #pragma unroll
-    for (int st = 0; st < S; ++st) {
-      float v[NVAL];
+    for (int r = 0; r < R; ++r) {
+      const uint32_t roff = row_off(nxt, r);
 #pragma unroll
-      for (int i = 0; i < RS; ++i) {
-        const int r = st * RS + i;
-        float g = 0.f, u = 0.f;
+      for (int c = 0; c < CPL; ++c)  // lanes past the slice accumulate values never written
+        T::axpy(yacc[c], act[r], as_uint4(dw[r][c]));
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) {  // lanes past the slice hold zeros
-          g = T::dot(gw[r][c], xr[c], g);
-          u = T::dot(uw[r][c], xr[c], u);
-        }
-        v[i] = g;
-        v[RS + i] = u;
-      }
-      wave_reduce_scatter<NVAL>(v);  // lane l holds the wave sum of value l / G
-      float gs[RS], us[RS];
-      if (P > 1) {
-        // the P waves' sums of each value meet in LDS; lane (value, wave)
-        // reads one and a fixed shuffle tree over the PP lanes adds them
-        if (lane % G == 0) gu[st][team][lane / G][p] = v[0];
-        __syncthreads();
-        const int PP = a.PP, val = lane / PP, q = lane % PP;
-        float t = (val < NVAL && q < P) ? gu[st][team][val][q] : 0.f;
-        for (int m = PP / 2; m >= 1; m >>= 1) t += __shfl_xor(t, m, WAVE);
+      for (int c = 0; c < CPL; ++c)
 #pragma unroll
-        for (int i = 0; i < RS; ++i) {
-          gs[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), i * PP));
-          us[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), (RS + i) * PP));
-        }
-      } else {
+        for (int e = 0; e < V; ++e) asm volatile("" : "+v"(yacc[c][e]));
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < RS; ++i) {
-          gs[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[0]), i * G));
-          us[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[0]), (RS + i) * G));
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < RS; ++i) {
-        const int r = st * RS + i;
-        if (valid[r]) {  // lanes past the slice accumulate values never written
-          float act = gated(a.act, gs[i], us[i]);
-          if (fabsf(act) < thr) act = 0.f;
-#pragma unroll
-          for (int c = 0; c < CPL; ++c) T::axpy(yacc[c], act, dw[r][c]);
-        }
-      }
+      for (int c = 0; c < CPL; ++c) dw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], 2 * third);
     }
-    // with one stage, the next round's writes to gu must wait for this
-    // round's reads (with two, the other stage's barrier orders them)
-    if (S == 1 && P > 1) __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    cur = nxt;
+    nxt = nxt2;
   }
   // teams 1.. hand their partial y to team 0 through LDS (fixed order)
   if (teams > 1) {
@@ -444,13 +485,7 @@ __global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict
   }
   // the wave's 16 row groups of each piece: a fixed shuffle tree over lane
   // bits 2..5, leaving lane q with piece q's wave sum
-#pragma unroll
-  for (int m = 4; m < WAVE; m <<= 1) {
-    acc.x += __shfl_xor(acc.x, m, WAVE);
-    acc.y += __shfl_xor(acc.y, m, WAVE);
-    acc.z += __shfl_xor(acc.z, m, WAVE);
-    acc.w += __shfl_xor(acc.w, m, WAVE);
-  }
+  acc = make_float4(sum_quads(acc.x), sum_quads(acc.y), sum_quads(acc.z), sum_quads(acc.w));
   if (lane < 4) red[w][lane] = acc;
   __syncthreads();
   if (t < 4 && cok) {  // waves in order
@@ -619,7 +654,11 @@ static int env_int(const char* name, int dflt) {
 }
 
 // Workgroups of `kernel` that fit on the current device at once (cached).
+// The occupancy query divides the waves evenly over a compute unit's four
+// SIMDs, but two 9-wave workgroups may both want three waves of the same
+// SIMD: a workgroup counts as the next multiple of four waves.
 static int coresident(const void* kernel, int threads, size_t lds) {
+  threads = (threads + 4 * WAVE - 1) / (4 * WAVE) * (4 * WAVE);
   static std::mutex mu;
   static std::map<std::tuple<int, const void*, int, size_t>, int> cache;
   int dev = 0;
@@ -658,14 +697,13 @@ static void launch_rows_t(const MlpArgs& a, size_t lds, size_t lds_fused, bool w
 template <class T, int CPL, int R>
 static void launch_rows(const MlpArgs& a, size_t lds, size_t lds_fused, bool want_fused,
                         bool* fused, hipStream_t stream) {
-  const int threads = a.teams * a.P * WAVE;
-  if (threads <= 512) {  // up to 8 waves: a register budget of 256 per lane
-    launch_rows_t<T, CPL, R, 512>(a, lds, lds_fused, want_fused, fused, stream);
-  } else if constexpr (R == 8) {  // 9-10 waves: 168 registers per lane
-    if (threads <= 640) launch_rows_t<T, CPL, R, 640>(a, lds, lds_fused, want_fused, fused, stream);
-  } else if constexpr (R <= 4) {  // 128 registers per lane: at most 4 rows a round
-    launch_rows_t<T, CPL, R, 1024>(a, lds, lds_fused, want_fused, fused, stream);
+  if constexpr (R * CPL <= 4) {  // at most 128 registers: any workgroup size
+    if (a.teams * a.P * WAVE > 512) {
+      launch_rows_t<T, CPL, R, 1024>(a, lds, lds_fused, want_fused, fused, stream);
+      return;
+    }
   }
+  launch_rows_t<T, CPL, R, 512>(a, lds, lds_fused, want_fused, fused, stream);
 }
 
 // Where one call keeps its scratch.  The workspace path: partials in dev_ws
@@ -695,43 +733,42 @@ static hipError_t mlp_t(const np_shape& s, int layer, const void* x, const void*
   a.thr = thr;
   a.NV = s.d_model / V;
   // column slice per wave: 64 vectors (CPL = 1) while that needs at most 10
-  // waves, else 128 vectors (CPL = 2; 70B, d 8192: 8 waves with 4-row rounds
-  // take 33.6 us per call, 16 waves of 64 vectors 35.1)
+  // waves, else 128 vectors (CPL = 2; 70B, d 8192: 8 waves of 128 vectors
+  // take 26.2 us for the rows, 16 waves of 64 vectors 26.5)
   const int cpl = (a.NV + WAVE - 1) / WAVE <= 10 ? 1 : 2;
   a.P = (a.NV + WAVE * cpl - 1) / (WAVE * cpl);
-  int teams = env_int("NP_MLP_TEAMS", 1);
-  while (teams > 1 && teams * a.P > 16) teams /= 2;
+  // rows per team and round: 4 (with the registers refilled as they are
+  // used, more rows in flight gain nothing: 7B, k = 1651, 9.8 us for the
+  // rows with 4, 10.1 with 8), 2 for 128-vector slices over more than 8
+  // waves (128 registers per lane)
+  // Fewer than 512 rows: 2 a round on twice the workgroups (d 256, n = 400:
+  // 5.4 against 5.7 us per call)
+  int R = cpl == 1 ? env_int("NP_MLP_R", n_active < 512 ? 2 : 4) : (a.P <= 8 ? 4 : 2);
+  if (R != 2 && R != 8) R = cpl == 1 ? 4 : R;
+  if (R == 8 && a.P > 8) R = 4;
+  // narrow rows: up to 4 waves in row teams, while 128 workgroups would have
+  // a full round (us per call with 1, 2 and 4 teams: d 256 f16, P = 1, n =
+  // 5000: 9.2, 7.9, 7.4; d 512 f16, P = 1, 8000 dense rows: 11.7, 9.1, 9.0; d
+  // 1024 f16, P = 2, 20000 dense rows: 24.8, 23.2, 23.8; d 2048 f16, P = 4, n =
+  // 4000: 12.9, 13.4, 14.5)
+  int teams = 1;
+  while (2 * teams * a.P <= 4 && n_active >= 128 * R * 2 * teams) teams *= 2;
+  teams = env_int("NP_MLP_TEAMS", teams);
+  while (teams > 1 && teams * a.P > (R * cpl <= 4 ? 16 : 8)) teams /= 2;
   if (teams > 4) teams = 4;
   a.teams = teams;
-  // rows per team and round: 8 while the workgroup has at most 10 waves
-  // (168 or more registers per lane), 4 above that (128 registers), 2 for
-  // 128-vector slices (13B, d 5120, 10 waves: 8-row rounds 19.14 us per
-  // call, 4-row rounds 19.48)
-  int R = cpl == 1 ? env_int("NP_MLP_R", teams * a.P <= 10 ? 8 : 4) : (teams * a.P <= 8 ? 4 : 2);
-  // a small active set in 8-row rounds leaves most compute units idle: below
-  // 128 such workgroups, 4-row rounds on twice as many stream faster (7B
-  // shape, k = 550: 9.28 against 10.91 us per call; k = 1100, 138 workgroups
-  // of 8 rows: 11.74 against 12.85 with 4-row rounds)
-  if (R == 8 && !getenv("NP_MLP_R") && (n_active + 8 * teams - 1) / (8 * teams) < 128) R = 4;
-  if (R != 2 && R != 4) R = 8;
-  if (R == 8 && teams * a.P > 10) R = 4;
-  a.PP = 1;
-  while (a.PP < a.P) a.PP *= 2;
-  // the exchange holds 2 * (R / stages) values x PP waves in one wave's lanes
-  auto stage_rows = [&](int r) { return r >= 8 && teams * a.P > 8 ? r / 4 : (r >= 4 ? r / 2 : r); };
-  while (R > 2 && 2 * stage_rows(R) * a.PP > WAVE) R /= 2;
   // at most one workgroup per CU (256), as many rounds of R rows per team
   // as 256 workgroups would need, and the fewest workgroups that still
   // finish in that many rounds: fewer, fuller workgroups finish sooner and
-  // leave fewer partial sums (7B, k = 1651, one round: 207 workgroups take
-  // 15.05 us per call, 256 take 15.45, and 206 or fewer, which need a second
-  // round, about 18; 70B, k = 2867, three 4-row rounds: 239 workgroups 31.7
-  // us, 256 32.0)
+  // leave fewer partial sums (the rows alone, 7B, k = 1651, two 4-row rounds:
+  // 207 workgroups take 9.8 us, 236 and 256 10.1, 138 10.9; 70B, k = 2867,
+  // three rounds: 240 workgroups 26.2 us, 256 27.5)
   const int per = R * teams;
   const int rounds = (n_active + per * 256 - 1) / (per * 256);
   const int full = rounds > 0 ? (n_active + per * rounds - 1) / (per * rounds) : 1;
   const int target = std::min(env_int("NP_MLP_WG", full), sc ? sc->max_wg : MLP_MAX_WG);
-  int n_wg = n_active < target ? n_active : target;
+  int n_wg = std::max(n_active < target ? n_active : target,
+                      (n_active + MLP_WG_ROWS - 1) / MLP_WG_ROWS);
   if (n_wg < 1) n_wg = 1;
   a.n_wg = n_wg;
   a.n_active = n_active;

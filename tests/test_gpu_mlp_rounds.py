@@ -1,0 +1,74 @@
+"""The rows kernel of the sparse MLP at the edges of its launch rules: row
+counts on both sides of the 2- and 4-row rounds and of the row teams that
+narrow rows get, one- and two-vector slices over 1 to 16 waves in each type,
+more rows per workgroup than its threads load in one pass, and a row without
+a slot under an infinite x.  Records and x are dyadic (m 2^-6, |m| <= 1; x in
+{-1, 0, 1}), so every sum is exact in fp32 in any order and y must equal the
+oracle's value for value."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from paper_2608_22643_amd import binding as B
+from paper_2608_22643_amd import workload as W
+from gpu_util import DEV, Bufs, decode_y, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# (d, type, row counts, workgroups forced through NP_MLP_WG or None)
+CASES = [
+    (256, "f32", (3, 511, 512, 513), None),             # 1 wave, 2- and 4-row rounds
+    (264, "f16", (1023, 1024, 2047, 2048, 2051), None),  # 1 wave: 1, 2 and 4 teams, ragged width
+    (1000, "bf16", (511, 1023, 1024, 1500), None),       # 2 waves: 1 and 2 teams
+    (2048, "f32", (512, 1030), None),                    # 8 waves of one vector
+    (2568, "f32", (512, 600), None),                     # 6 waves of two vectors
+    (4608, "f16", (9, 517), None),                       # 9 waves
+    (8192, "bf16", (511, 1027), None),                   # 8 waves of two vectors
+    (8192, "f32", (257, 515), None),                     # 16 waves of two vectors
+    (16384, "bf16", (2, 513), None),                     # 16 waves of two vectors
+    (512, "f16", (1100, 1600), 1),                       # a range longer than the workgroup
+]
+
+
+@pytest.mark.parametrize("d,dt,rows,wg", CASES, ids=[f"d{c[0]}_{c[1]}" for c in CASES])
+def test_mlp_rounds_exact(d, dt, rows, wg, monkeypatch):
+    if wg:
+        monkeypatch.setenv("NP_MLP_WG", str(wg))
+    k = max(rows)
+    F, C = k + 40, k + 20
+    cfg = W.Config("rounds", 1, d, F, 8, k / F, C / F, dt, dt, 1, rho_given=0.0, k_override=k,
+                   c_override=C, dyadic=True, dyadic_w_range=1, dyadic_h_range=1)
+    say(f"[mlp rounds] d {d} {dt} rows {rows}")
+    bufs = Bufs(cfg)
+    bufs.reset()
+    rng = np.random.default_rng(d + k)
+    store, h = W.storage(cfg), W.hidden(cfg, 1)[0]
+    neuron = rng.permutation(F)[:C].astype(np.int32)
+    res, x = to_dev(store[0][neuron]), to_dev(h)
+    slots = rng.permutation(C)[:k].astype(np.int32)
+    y = torch.zeros(d * W.ITEMSIZE[dt], dtype=torch.uint8, device=DEV)
+    xv = orc.decode(dt, h)
+    rec = orc.decode(dt, store[0][neuron[slots]])
+    a = np.maximum(rec[:, :d] @ xv, 0) * (rec[:, d:2 * d] @ xv)
+    assert np.max(np.abs(a)) < 2.0 ** 12 and np.max(np.abs(a) @ np.abs(rec[:, 2 * d:])) < 2.0 ** 6
+    for n in rows:
+        B.np_sparse_mlp(bufs.shape, 0, x, res, to_dev(slots), n, y, bufs.ws)
+        torch.cuda.synchronize()
+        ref = orc.sparse_mlp(cfg, 0, h, store, neuron[slots[:n]])
+        assert np.array_equal(decode_y(orc, dt, y.cpu().numpy()), decode_y(orc, dt, ref)), n
+    # the dense call: every record of one layer, in order
+    B.np_dense_mlp(bufs.shape, to_dev(store[0]), x, y, bufs.ws)
+    torch.cuda.synchronize()
+    ref = orc.sparse_mlp(cfg, 0, h, store, np.arange(F, dtype=np.int32))
+    assert np.array_equal(decode_y(orc, dt, y.cpu().numpy()), decode_y(orc, dt, ref)), "dense"
+    assert B.np_device_error(bufs.ws) == 0
+    # rows without a slot add nothing, also where x is infinite
+    bad = np.full(k, -1, np.int32)
+    bad[::2] = C + 3
+    inf = torch.full((d,), float("inf"), dtype={"f32": torch.float32, "f16": torch.float16,
+                                                "bf16": torch.bfloat16}[dt], device=DEV)
+    B.np_sparse_mlp(bufs.shape, 0, inf, res, to_dev(bad), k, y, bufs.ws)
+    torch.cuda.synchronize()
+    assert np.all(decode_y(orc, dt, y.cpu().numpy()) == 0)
+    assert B.np_device_error(bufs.ws) == B.NP_DEVERR_NOT_RESIDENT
