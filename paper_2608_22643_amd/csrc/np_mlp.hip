@@ -758,14 +758,18 @@ static hipError_t mlp_t(const np_shape& s, int layer, const void* x, const void*
   if (teams > 4) teams = 4;
   a.teams = teams;
   // at most one workgroup per CU (256), as many rounds of R rows per team
-  // as 256 workgroups would need, and the fewest workgroups that still
-  // finish in that many rounds: fewer, fuller workgroups finish sooner and
-  // leave fewer partial sums (the rows alone, 7B, k = 1651, two 4-row rounds:
-  // 207 workgroups take 9.8 us, 236 and 256 10.1, 138 10.9; 70B, k = 2867,
-  // three rounds: 240 workgroups 26.2 us, 256 27.5)
+  // as they need, and the fewest workgroups that still finish in that many
+  // rounds: fewer, fuller workgroups leave fewer partial sums, and about 200
+  // already draw the full HBM rate (us per call, 7B, k = 1651, two 4-row
+  // rounds: 207 workgroups 12.2, 236 12.4, 256 12.5).  So above 208 another
+  // round is added while 180 are left (70B, k = 2867: 180 workgroups 29.7, 239
+  // 30.7, 256 31.3; SwiGLU, 4670 rows: 195 23.1, 234 23.5; 7B dense: 197 43.4,
+  // 256 45.1; below 180: 7B, 165 12.9; d 3000 f32, k = 2500, 157 22.4, 209 20.5)
   const int per = R * teams;
-  const int rounds = (n_active + per * 256 - 1) / (per * 256);
-  const int full = rounds > 0 ? (n_active + per * rounds - 1) / (per * rounds) : 1;
+  int rounds = std::max(1, (n_active + per * 256 - 1) / (per * 256));
+  auto wgs = [&](int r) { return (n_active + per * r - 1) / (per * r); };
+  while (wgs(rounds) > 208 && wgs(rounds + 1) >= 180) ++rounds;
+  const int full = std::max(1, wgs(rounds));
   const int target = std::min(env_int("NP_MLP_WG", full), sc ? sc->max_wg : MLP_MAX_WG);
   int n_wg = std::max(n_active < target ? n_active : target,
                       (n_active + MLP_WG_ROWS - 1) / MLP_WG_ROWS);
