@@ -502,7 +502,7 @@ np_status np_sparse_mlp_t(const np_shape* shape, int32_t layer, const void* x,
  * projections are matrix products over the batch, run on the matrix cores
  * (MFMA, fp32 accumulation); acts is not rounded further.  Requires
  * 1 <= n <= 65536, F * 3d * sizeof(w) < 2^31 and n * d * sizeof(a) < 2^31.
- * A launch per 128 tokens on `stream`; dev_ws is not used (may be NULL). */
+ * One kernel on `stream`; dev_ws is not used (may be NULL). */
 np_status np_act_batch(const np_shape* shape, const void* weights, const void* x, int32_t n,
                        float* acts, void* dev_ws, hipStream_t stream);
 

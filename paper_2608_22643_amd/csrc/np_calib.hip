@@ -20,197 +20,243 @@ namespace np {
 // elements.  Lane l holds row l%16 of the A operand (a neuron's gate or up
 // row) and column l%16 of the B operand (a token), each as the V consecutive
 // elements starting at step*4V + V*(l/16), so the two operands pair the same
-// reduction indices whatever order the unit sums them in, and one 16-byte
-// load instruction reads 64 contiguous bytes of each of 16 rows.  The
-// accumulator layout: lane l, register r holds output row 4*(l/16) + r
-// (neuron) and column l%16 (token).
+// reduction indices whatever order the unit sums them in.  The accumulator
+// layout: lane l, register r holds output row 4*(l/16) + r (neuron) and
+// column l%16 (token).
 //
-// A workgroup owns 64 neurons (four row tiles) and every token of the launch
-// (up to 128: eight 16-token tiles); wave w takes token tiles w and w + 4 of
-// every row tile over the whole reduction, so no wave needs another's sums,
-// and each token fragment a wave loads serves four row tiles.  The neurons' gate and up
-// rows, and the chunk's token rows, stream through LDS in chunks of KC
-// elements: the workgroup loads a chunk with whole-line 16-byte loads (16
-// lanes per 256-byte row piece) into one of two buffers while the waves
-// multiply the other, and each wave reads its MFMA fragments from LDS (rows
-// padded by 16 bytes: no bank conflicts).
-constexpr int AB_WAVES = 4;
-constexpr int AB_NB = 64;         // neurons of a workgroup (AB_NB / 16 row tiles)
-constexpr int AB_MAX_TILES = 8;   // token tiles of 16
-constexpr int AB_ROWB = 256;      // bytes of a row piece per chunk
-constexpr int AB_PITCH = AB_ROWB + 16;
+// A workgroup of 8 waves owns a block of BM neurons (2 BM weight rows) x BN
+// tokens, wave (i, j) of its WGM x WGN waves MT x NT tiles of it (gate and up
+// of the same neurons, so that the activation needs no exchange).  The rows
+// stream through LDS in pieces of ROWB bytes, double buffered (row pitch
+// ROWB + 16 bytes: a fragment read touches every bank once).  In each
+// iteration a thread writes the pieces it holds in registers to the other
+// buffer, refills the registers from memory halfway through the products of
+// the current buffer, and one barrier, for LDS only, ends the iteration: a
+// load has at least an iteration (two with DEPTH 2) to arrive.
+//
+// Two regimes.  Up to 128 tokens it is HBM-bound (n flops per weight byte):
+// small blocks, so that all CUs stream, long pieces (fewer barriers), the
+// nontemporal hint on weights that one block reads.  SwiGLU 7B layer (14336 x
+// 4096 f16, 235 MB of weights), 128 tokens: 60.2 us, 64 tokens 48.4 us (a plain
+// read of the same rows 43.8 us); with 128-byte pieces 64 and 51; the
+// four-wave kernel before, whose loads the compiler had put behind the
+// products they were to overlap, 76.5 and 68.7.  Beyond, it is bound by the
+// matrix cores and by what feeds them: a 128 x 256 block reads 96 bytes of LDS
+// a cycle for 8 waves of 128 x 64 outputs, and each weight row once per 256
+// tokens.  13B layer (13824 x 5120 f16), 1999 tokens: 560-588 us (962-1011
+// TFLOP/s) against 1355 in launches of 128 tokens; 4096 tokens on the SwiGLU
+// layer 824-868 us (1108-1168 TFLOP/s; 2300 before; the library's square
+// product of size 8192: 1112-1164 TFLOP/s).
+constexpr int AB_WAVES = 8;
+constexpr int AB_NT = AB_WAVES * WAVE;
 
 struct ActBatchArgs {
   const void* w;    // one layer's [F][3d] records
-  const void* x;    // [n][d] tokens of this launch
-  float* acts;      // [n][F] rows of this launch
+  const void* x;    // [n][d] tokens
+  float* acts;      // [n][F]
   uint32_t w_bytes, x_bytes;
   int F, d, n, act;
+  int fb, tb;       // neuron blocks, token blocks
 };
 
-template <class T, int TPW>
-__global__ __launch_bounds__(AB_WAVES * WAVE) void act_batch_kernel(ActBatchArgs a) {
-  constexpr int V = T::V, ESZ = 16 / V, KS = 4 * V;  // KS: reduction elements per MFMA step
-  constexpr int KC = AB_ROWB / ESZ;                  // reduction elements per chunk
-  constexpr int SPC = KC / KS;                       // MFMA steps per chunk (4)
-  constexpr int MT = AB_NB / 16;                      // row tiles
-  constexpr int PIECES = 2 * AB_NB * (AB_ROWB / 16);  // 16-byte pieces of a chunk (g and u)
-  constexpr int PPT = PIECES / (AB_WAVES * WAVE);    // pieces per thread (8)
-  __shared__ __attribute__((aligned(16))) char lds[2][2][AB_NB][AB_PITCH];  // buffer, g/u, row
-  // the chunk's token pieces: buffer, token, 16-byte column (padded rows)
-  __shared__ __attribute__((aligned(16))) char xs[2][16 * AB_MAX_TILES][AB_PITCH];
-  constexpr int XPT = 16 * AB_MAX_TILES * (AB_ROWB / 16) / (AB_WAVES * WAVE);  // token pieces per thread (8)
-  const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE, grp = lane / 16;
-  const int n0 = blockIdx.x * AB_NB;
+template <int MT_, int NT_, int WGM_, int WGN_, int DEPTH_, int ROWB_>
+struct AbTile {
+  static constexpr int ROWB = ROWB_, PITCH = ROWB + 16;
+  static constexpr int MT = MT_, NT = NT_, WGM = WGM_, WGN = WGN_, DEPTH = DEPTH_;
+  static constexpr int BM = 16 * MT * WGM, BN = 16 * NT * WGN;
+  static constexpr int ROWS = 2 * BM + BN;               // LDS rows: gate, up, tokens
+  static constexpr int PIECES = ROWS * (ROWB / 16);   // 16-byte pieces of an iteration
+  static constexpr int PPT = PIECES / AB_NT;             // per thread
+  static constexpr size_t LDS = (size_t)2 * ROWS * PITCH;
+  static_assert(WGM * WGN == AB_WAVES && PIECES % AB_NT == 0 &&
+                    2 * BM % (AB_NT / (ROWB / 16)) == 0,
+                "whole pieces per thread, weights and tokens in separate ones");
+};
+
+template <class T, class C, bool NTW>
+__global__ __launch_bounds__(AB_NT) void act_batch_kernel(ActBatchArgs a) {
+  constexpr int V = T::V, ESZ = 16 / V, KC = C::ROWB / ESZ;  // KC: elements per iteration
+  constexpr int ROWB = C::ROWB, PITCH = C::PITCH, LPR = ROWB / 16;  // LPR: lanes of a row piece
+  constexpr int RPP = AB_NT / LPR;  // rows of a piece index
+  constexpr int MT = C::MT, NT = C::NT, PPT = C::PPT, DEPTH = C::DEPTH;
+  __shared__ __attribute__((aligned(16))) char ab_lds[C::LDS];
+  const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE, grp = lane / 16, li = lane & 15;
+  const int wm = w / C::WGN, wn = w % C::WGN;
+  // blocks b, b + 8, ... run on one XCD: each XCD takes a contiguous run of
+  // blocks, token blocks innermost, so its L2 serves a weight panel to the
+  // token blocks that share it
+  const int nb = a.fb * a.tb, per = (nb + 7) / 8;
+  const int blk = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+  if (blk >= nb || (int)(blockIdx.x / 8) >= per) return;
+  const int f0 = blk / a.tb * C::BM, t0 = blk % a.tb * C::BN;
   const __amdgpu_buffer_rsrc_t wr = make_rsrc(a.w, a.w_bytes), xr = make_rsrc(a.x, a.x_bytes);
-  const uint32_t rec = (uint32_t)(3 * a.d * ESZ), dbytes = (uint32_t)(a.d * ESZ);
-  const int chunks = (a.d + KC - 1) / KC;
-  // this thread's pieces of every chunk: piece p -> (projection, row, 16-byte column)
-  uint32_t p_off[PPT];  // byte offset at reduction index 0, or OOB
-  int p_col[PPT];
+  const uint32_t dbytes = (uint32_t)(a.d * ESZ), rec = 3u * dbytes;
+  const int iters = (a.d + KC - 1) / KC;
+  // piece i of this thread: row t / LPR + RPP i, 16-byte column t % LPR (gate
+  // rows, up rows, tokens); rows past F or n read out of range: zeros
+  const uint32_t col = (uint32_t)(t % LPR) * 16u;
+  uint32_t off[PPT];
 #pragma unroll
   for (int i = 0; i < PPT; ++i) {
-    const int pc = t + AB_WAVES * WAVE * i;
-    const int proj = pc / (PIECES / 2), row = (pc / (AB_ROWB / 16)) % AB_NB, col = pc % (AB_ROWB / 16);
-    const int neuron = n0 + row;
-    p_off[i] = neuron < a.F ? (uint32_t)neuron * rec + (uint32_t)proj * dbytes : BUF_OOB;
-    p_col[i] = col;
+    const int row = t / LPR + RPP * i;
+    if (row < 2 * C::BM) {
+      const int f = f0 + row % C::BM;
+      off[i] = f < a.F ? (uint32_t)f * rec + (uint32_t)(row / C::BM) * dbytes : BUF_OOB;
+    } else {
+      const int tok = t0 + row - 2 * C::BM;
+      off[i] = tok < a.n ? (uint32_t)tok * dbytes : BUF_OOB;
+    }
   }
-  auto load_chunk = [&](int c, uint4* r) {
+  auto load = [&](int it, u32x4_t* r) {  // past d: zeros
+    const uint32_t k = (uint32_t)it * ROWB + col;
 #pragma unroll
     for (int i = 0; i < PPT; ++i) {
-      const int k = c * KC + p_col[i] * V;  // first element of the piece
-      r[i] = buf_load16_nt(wr, (p_off[i] != BUF_OOB && k < a.d) ? p_off[i] + (uint32_t)k * ESZ
-                                                             : BUF_OOB, 0);
+      const uint32_t o = k < dbytes && off[i] != BUF_OOB ? off[i] + k : BUF_OOB;
+      if (RPP * i < 2 * C::BM)  // a piece index holds weight rows only or tokens only
+        r[i] = NTW ? buf_load16v_nt(wr, o, 0) : buf_load16v(wr, o, 0);
+      else
+        r[i] = buf_load16v(xr, o, 0);
     }
   };
-  auto store_chunk = [&](int buf, const uint4* r) {
+  char* const st = ab_lds + (size_t)(t / LPR) * PITCH + col;
+  auto store = [&](int buf, const u32x4_t* r) {
+    char* p = st + (size_t)buf * C::ROWS * PITCH;
 #pragma unroll
-    for (int i = 0; i < PPT; ++i) {
-      const int pc = t + AB_WAVES * WAVE * i;
-      const int proj = pc / (PIECES / 2), row = (pc / (AB_ROWB / 16)) % AB_NB, col = pc % (AB_ROWB / 16);
-      *(uint4*)&lds[buf][proj][row][col * 16] = r[i];
-    }
+    for (int i = 0; i < PPT; ++i) *(u32x4_t*)(p + (size_t)RPP * i * PITCH) = r[i];
   };
-  // the chunk's token pieces, whole 256-byte row pieces per 16 lanes like
-  // the weights (a fragment load straight from memory would touch 16 token
-  // rows per instruction): piece p -> token p / 16, 16-byte column p % 16
-  uint32_t x_off[XPT];  // byte offset at reduction index 0, or OOB
-#pragma unroll
-  for (int i = 0; i < XPT; ++i) {
-    const int pc = t + AB_WAVES * WAVE * i, tok = pc / (AB_ROWB / 16);
-    x_off[i] = tok < a.n ? (uint32_t)tok * dbytes : BUF_OOB;
-  }
-  auto load_xchunk = [&](int c, uint4* r) {
-#pragma unroll
-    for (int i = 0; i < XPT; ++i) {
-      const int pc = t + AB_WAVES * WAVE * i;
-      const int k = c * KC + (pc % (AB_ROWB / 16)) * V;
-      r[i] = buf_load16(xr, (x_off[i] != BUF_OOB && k < a.d) ? x_off[i] + (uint32_t)k * ESZ
-                                                             : BUF_OOB, 0);
-    }
-  };
-  auto store_xchunk = [&](int buf, const uint4* r) {
-#pragma unroll
-    for (int i = 0; i < XPT; ++i) {
-      const int pc = t + AB_WAVES * WAVE * i;
-      *(uint4*)&xs[buf][pc / (AB_ROWB / 16)][(pc % (AB_ROWB / 16)) * 16] = r[i];
-    }
-  };
-  f32x4 accg[MT][TPW], accu[MT][TPW];
+  f32x4 accg[MT][NT], accu[MT][NT];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int j = 0; j < TPW; ++j)
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) accg[m][j][r] = accu[m][j][r] = 0.f;
-
-  uint4 pre[PPT], prex[XPT];
-  load_chunk(0, pre);
-  load_xchunk(0, prex);
-  store_chunk(0, pre);
-  store_xchunk(0, prex);
-  __syncthreads();
-  for (int c = 0; c < chunks; ++c) {
-    const int buf = c & 1;
-    if (c + 1 < chunks) {  // the next chunk is in flight during this one's products
-      load_chunk(c + 1, pre);
-      load_xchunk(c + 1, prex);
-    }
+  // fragment addresses: gate rows of this wave's first tile, tokens likewise
+  const char* const fg = ab_lds + (size_t)(wm * MT * 16 + li) * PITCH + grp * 16;
+  const char* const fx = ab_lds + (size_t)(2 * C::BM + wn * NT * 16 + li) * PITCH + grp * 16;
+  auto multiply = [&](int buf, int s_begin, int s_end) {
+    const size_t bo = (size_t)buf * C::ROWS * PITCH;
 #pragma unroll
-    for (int s = 0; s < SPC; ++s) {
-      uint4 b[TPW];  // token tile w + 4j: token 16 (w + 4j) + lane % 16
+    for (int s = s_begin; s < s_end; ++s) {
+      uint4 b[NT];
 #pragma unroll
-      for (int j = 0; j < TPW; ++j)
-        b[j] = *(const uint4*)&xs[buf][(w + AB_WAVES * j) * 16 + (lane & 15)][s * 64 + grp * 16];
+      for (int j = 0; j < NT; ++j)
+        b[j] = *(const uint4*)(fx + bo + (size_t)16 * j * PITCH + s * 64);
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
-        const int row = 16 * m + (lane & 15);
-        const uint4 ag = *(const uint4*)&lds[buf][0][row][s * 64 + grp * 16];
-        const uint4 au = *(const uint4*)&lds[buf][1][row][s * 64 + grp * 16];
+        const uint4 ag = *(const uint4*)(fg + bo + (size_t)16 * m * PITCH + s * 64);
+        const uint4 au = *(const uint4*)(fg + bo + (size_t)(C::BM + 16 * m) * PITCH + s * 64);
 #pragma unroll
-        for (int j = 0; j < TPW; ++j) {
+        for (int j = 0; j < NT; ++j) {
           accg[m][j] = mfma_step<T>(ag, b[j], accg[m][j]);
           accu[m][j] = mfma_step<T>(au, b[j], accu[m][j]);
         }
       }
     }
-    if (c + 1 < chunks) {
-      store_chunk(buf ^ 1, pre);
-      store_xchunk(buf ^ 1, prex);
+  };
+  u32x4_t pre[DEPTH][PPT];
+  load(0, pre[0]);
+  store(0, pre[0]);
+#pragma unroll
+  for (int q = 0; q < DEPTH; ++q) load(1 + q, pre[q]);
+  lds_barrier();
+  // iteration it: registers pre[it % DEPTH] hold piece it + 1
+  for (int it = 0;; it += 2 * DEPTH) {
+#pragma unroll
+    for (int q = 0; q < 2 * DEPTH; ++q) {
+      store((q + 1) & 1, pre[q % DEPTH]);
+      multiply(q & 1, 0, ROWB / 128);
+      __builtin_amdgcn_sched_barrier(0);  // neither ahead of the stores nor behind the products
+      load(it + q + 1 + DEPTH, pre[q % DEPTH]);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(q & 1, ROWB / 128, ROWB / 64);
+      if (it + q + 1 >= iters) goto done;  // (a skipped iteration would blur the load counts)
+      lds_barrier();
     }
-    __syncthreads();  // the other buffer is complete; this one may be overwritten next
   }
+done:
   // acts[token][neuron]: lane l, register r holds neuron 16 m + 4 (l / 16) + r
 #pragma unroll
-  for (int j = 0; j < TPW; ++j) {
-    const int tok = (w + AB_WAVES * j) * 16 + (lane & 15);
+  for (int j = 0; j < NT; ++j) {
+    const int tok = t0 + (wn * NT + j) * 16 + li;
     if (tok >= a.n) continue;
     float* dst = a.acts + (size_t)tok * a.F;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
-      const int nb = n0 + 16 * m + 4 * grp;  // neurons nb .. nb + 3
+      const int f = f0 + (wm * MT + m) * 16 + 4 * grp;  // neurons f .. f + 3
       float o[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = gated(a.act, accg[m][j][e], accu[m][j][e]);
       if ((a.F & 3) == 0) {
-        if (nb < a.F) *(float4*)(dst + nb) = make_float4(o[0], o[1], o[2], o[3]);
+        if (f < a.F) *(float4*)(dst + f) = make_float4(o[0], o[1], o[2], o[3]);
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (nb + e < a.F) dst[nb + e] = o[e];
+          if (f + e < a.F) dst[f + e] = o[e];
       }
     }
   }
+}
+
+template <class T, class C, bool NTW>
+static hipError_t launch_ab(const ActBatchArgs& a, hipStream_t stream) {
+  ActBatchArgs b = a;
+  b.fb = (a.F + C::BM - 1) / C::BM;
+  b.tb = (a.n + C::BN - 1) / C::BN;
+  hipLaunchKernelGGL((act_batch_kernel<T, C, NTW>), dim3((b.fb * b.tb + 7) / 8 * 8), dim3(AB_NT),
+                     0, stream, b);
+  return hipGetLastError();
 }
 
 template <class T>
 static hipError_t act_batch_t(const np_shape& s, const void* weights, const void* x, int n,
                               float* acts, hipStream_t stream) {
   constexpr int ESZ = 16 / T::V;
-  const int tiles = (s.d_ffn + AB_NB - 1) / AB_NB;
-  for (int i0 = 0; i0 < n; i0 += 16 * AB_MAX_TILES) {
-    ActBatchArgs a;
-    a.w = weights;
-    a.x = (const char*)x + (size_t)i0 * s.d_model * ESZ;
-    a.acts = acts + (size_t)i0 * s.d_ffn;
-    a.n = std::min(n - i0, 16 * AB_MAX_TILES);
-    a.w_bytes = (uint32_t)((size_t)s.d_ffn * 3 * s.d_model * ESZ);
-    a.x_bytes = (uint32_t)((size_t)a.n * s.d_model * ESZ);
-    a.F = s.d_ffn;
-    a.d = s.d_model;
-    a.act = s.act;
-    const int ntt = (a.n + 15) / 16;  // token tiles; wave w takes tiles w, w + 4
-    if (ntt <= AB_WAVES)
-      hipLaunchKernelGGL((act_batch_kernel<T, 1>), dim3(tiles), dim3(AB_WAVES * WAVE), 0, stream,
-                         a);
-    else
-      hipLaunchKernelGGL((act_batch_kernel<T, 2>), dim3(tiles), dim3(AB_WAVES * WAVE), 0, stream,
-                         a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+  ActBatchArgs a;
+  a.w = weights;
+  a.x = x;
+  a.acts = acts;
+  a.n = n;
+  a.w_bytes = (uint32_t)((size_t)s.d_ffn * 3 * s.d_model * ESZ);
+  a.x_bytes = (uint32_t)((size_t)n * s.d_model * ESZ);
+  a.F = s.d_ffn;
+  a.d = s.d_model;
+  a.act = s.act;
+  // The block whose rounds over the 256 CUs cost least: the time of a round
+  // of each block, relative to each other (d 4096: 119, 74, 51 and 33 us in
+  // f16; fp32 is bound by its matrix rate and goes by the area alone), is the
+  // same for any size within 10%: f16, n = 256, F = 14336, one round of 128 x
+  // 128 takes 84 us, one of 128 x 256 115, two of 64 x 128 97; n = 1500, d 600,
+  // F = 2000, one round of 128 x 128 17, one of 128 x 256 24, two of 64 x 128 21.
+  struct Block {
+    int bm, bn;
+    float cost16, cost32;
+  };
+  static constexpr Block blocks[4] = {
+      {128, 256, 119.f, 6.4f}, {128, 128, 74.f, 3.3f}, {64, 128, 51.f, 1.8f}, {64, 64, 33.f, 1.f}};
+  int best = 0;
+  float least = 0.f;
+  for (int i = 0; i < 4; ++i) {
+    const Block& q = blocks[i];
+    const long long nb = (long long)((a.F + q.bm - 1) / q.bm) * ((n + q.bn - 1) / q.bn);
+    const float c = (float)((nb + 255) / 256) * (T::dtype == NP_F32 ? q.cost32 : q.cost16);
+    if (i == 0 || c < least) {
+      best = i;
+      least = c;
+    }
   }
-  return hipSuccess;
+  // weights that a single token block reads need not stay in the caches
+  const bool once = n <= blocks[best].bn;
+  switch (best) {
+    case 0: return launch_ab<T, AbTile<4, 4, 2, 4, 1, 128>, false>(a, stream);
+    case 1: return launch_ab<T, AbTile<2, 4, 4, 2, 2, 128>, false>(a, stream);
+    case 2:
+      return once ? launch_ab<T, AbTile<1, 4, 4, 2, 1, 256>, true>(a, stream)
+                  : launch_ab<T, AbTile<1, 4, 4, 2, 1, 256>, false>(a, stream);
+    default:
+      return once ? launch_ab<T, AbTile<1, 2, 4, 2, 1, 256>, true>(a, stream)
+                  : launch_ab<T, AbTile<1, 2, 4, 2, 1, 256>, false>(a, stream);
+  }
 }
 
 hipError_t launch_act_batch(const np_shape& s, const void* weights, const void* x, int n,
