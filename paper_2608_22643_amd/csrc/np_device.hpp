@@ -338,37 +338,66 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-__device__ inline uint32_t wave_incl_scan(uint32_t v) {
-  const int lane = threadIdx.x & (WAVE - 1);
-#pragma unroll
-  for (int off = 1; off < WAVE; off <<= 1) {
-    uint32_t y = __shfl_up(v, off, WAVE);
-    if (lane >= off) v += y;
-  }
+// Inclusive prefix sum over the wave's lanes, in register moves (DPP): within
+// rows of 16 lanes, then the row totals carried up.  Lanes without a source
+// add zero.  Every lane of the wave takes part.
+template <int CTRL, int ROWS>
+__device__ inline uint32_t dpp_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ inline uint32_t row_incl_scan(uint32_t v) {  // within rows of 16 lanes
+  v += dpp_or_zero<0x111, 0xF>(v);  // row_shr:1
+  v += dpp_or_zero<0x112, 0xF>(v);  // row_shr:2
+  v += dpp_or_zero<0x114, 0xF>(v);  // row_shr:4
+  v += dpp_or_zero<0x118, 0xF>(v);  // row_shr:8
   return v;
+}
+__device__ inline uint32_t wave_incl_scan(uint32_t v) {
+  v = row_incl_scan(v);
+  v += dpp_or_zero<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+__device__ inline uint32_t wave_total(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), WAVE - 1);
+}
+__device__ inline uint32_t wave_max(uint32_t v) {
+  auto step = [&](uint32_t o) { v = o > v ? o : v; };
+  step(dpp_or_zero<0x111, 0xF>(v));
+  step(dpp_or_zero<0x112, 0xF>(v));
+  step(dpp_or_zero<0x114, 0xF>(v));
+  step(dpp_or_zero<0x118, 0xF>(v));
+  step(dpp_or_zero<0x142, 0xA>(v));
+  step(dpp_or_zero<0x143, 0xC>(v));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, WAVE - 1);
 }
 
 // Exclusive prefix sum over the NT threads of a workgroup, in thread order.
-// lds must hold NT/64 + 1 uint32.  Returns the exclusive value; *total gets
-// the sum.  Contains barriers: every thread must call it.
+// lds must hold NT/64 uint32.  Returns the exclusive value; *total gets the
+// sum.  One barrier (lds_barrier): every thread must call it, and lds must
+// not be written again before another barrier.
+template <int NT>
+__device__ inline uint32_t block_excl_scan_once(uint32_t v, uint32_t* lds, uint32_t* total) {
+  constexpr int NW = NT / WAVE;
+  static_assert(NW <= 16, "the wave totals are one row of lanes");
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
+  const uint32_t incl = wave_incl_scan(v);
+  if (lane == WAVE - 1) lds[w] = incl;
+  lds_barrier();
+  const uint32_t t = row_incl_scan(lane < NW ? lds[lane] : 0u);
+  const uint32_t before =
+      w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)t, w > 0 ? w - 1 : 0) : 0u;
+  *total = (uint32_t)__builtin_amdgcn_readlane((int)t, NW - 1);
+  return before + incl - v;
+}
+
+// The same with lds free for reuse on return (a second barrier).
 template <int NT>
 __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t* lds, uint32_t* total) {
-  constexpr int NW = NT / WAVE;
-  const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
-  uint32_t incl = wave_incl_scan(v);
-  if (lane == WAVE - 1) lds[w] = incl;
+  const uint32_t r = block_excl_scan_once<NT>(v, lds, total);
   __syncthreads();
-  if (w == 0) {
-    uint32_t t = lane < NW ? lds[lane] : 0u;
-    uint32_t ti = wave_incl_scan(t);
-    if (lane < NW) lds[lane] = ti - t;
-    if (lane == NW - 1) lds[NW] = ti;
-  }
-  __syncthreads();
-  uint32_t res = lds[w] + incl - v;
-  *total = lds[NW];
-  __syncthreads();
-  return res;
+  return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -389,8 +418,8 @@ __device__ inline void raise_error(void* ws, int bits) {
 
 // ---------------------------------------------------------------------------
 // k-selection over one workgroup (NT threads).  Each thread owns WPT
-// consecutive 32-id words (thread t: words t*WPT .. t*WPT+WPT-1), and key[w][b]
-// is the 32-bit unsigned key of id 32*(t*WPT+w)+b.  Selects the `kk` largest
+// consecutive KB-id words (thread t: words t*WPT .. t*WPT+WPT-1), and key[w][b]
+// is the 32-bit unsigned key of id KB*(t*WPT+w)+b.  Selects the `kk` largest
 // keys; ties at the kk-th key go to the smaller ids.  On return sel[w] holds
 // the selected bits of each owned word.
 //
@@ -411,8 +440,8 @@ __device__ inline void raise_error(void* ws, int bits) {
 // ---------------------------------------------------------------------------
 constexpr uint32_t SEL_SMALL_CAND = 1024;  // at most this many keys left: 8-bit passes
 
-template <int NT, int WPT>
-__device__ inline void block_select_largest(const uint32_t (&key)[WPT][32], uint32_t kk,
+template <int NT, int WPT, int KB>
+__device__ inline void block_select_largest(const uint32_t (&key)[WPT][KB], uint32_t kk,
                                             uint32_t (&sel)[WPT], uint32_t* hist,
                                             uint32_t* scan, uint32_t* res) {
   constexpr int NW = NT / WAVE;
@@ -422,7 +451,7 @@ __device__ inline void block_select_largest(const uint32_t (&key)[WPT][32], uint
 #pragma unroll
   for (int i = 0; i < WPT; ++i)
 #pragma unroll
-    for (int b = 0; b < 32; ++b) {
+    for (int b = 0; b < KB; ++b) {
       const uint32_t kv = key[i][b];
       nz += kv != 0u;
       kmax = kv > kmax ? kv : kmax;
@@ -476,7 +505,7 @@ __device__ inline void block_select_largest(const uint32_t (&key)[WPT][32], uint
 #pragma unroll
       for (int i = 0; i < WPT; ++i)
 #pragma unroll
-        for (int b = 0; b < 32; ++b) {
+        for (int b = 0; b < KB; ++b) {
           const uint32_t kv = key[i][b];
           if (kv != 0u && (kv & pmask) == prefix) atomicAdd(&hist[(kv >> shift) & (nb - 1)], 1u);
         }
@@ -546,7 +575,7 @@ __device__ inline void block_select_largest(const uint32_t (&key)[WPT][32], uint
 #pragma unroll
         for (int i = 0; i < WPT; ++i)
 #pragma unroll
-          for (int b = 0; b < 32; ++b) {
+          for (int b = 0; b < KB; ++b) {
             const uint32_t kv = key[i][b];
             if (kv != 0u && (kv & pmask) == prefix && kv < kmn) kmn = kv;
           }
@@ -573,7 +602,7 @@ __device__ inline void block_select_largest(const uint32_t (&key)[WPT][32], uint
   for (int i = 0; i < WPT; ++i) {
     uint32_t gt = 0, eq = 0;
 #pragma unroll
-    for (int b = 0; b < 32; ++b) {
+    for (int b = 0; b < KB; ++b) {
       gt |= (key[i][b] > prefix ? 1u : 0u) << b;
       eq |= (key[i][b] == prefix ? 1u : 0u) << b;
     }

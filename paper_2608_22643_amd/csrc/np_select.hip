@@ -1,10 +1,13 @@
 // np_select.hip -- fixed-size active sets and the delta against the resident
 // buffer (Sec. 3.4).  Both steps are small, latency-bound integer work: one
-// 1024-thread workgroup per downstream layer, ids owned in 32-bit words so
-// that set membership, ordering and compaction are bit operations, popcounts
-// and workgroup prefix sums.  Both share the radix k-selection primitive of
-// np_device.hpp (top-k of the scores; least-recently-used victims).
+// workgroup per downstream layer, ids owned in contiguous runs of bits so that
+// set membership, ordering and compaction are bit operations, popcounts and
+// workgroup prefix sums.  The general path of either is the radix k-selection
+// primitive of np_device.hpp (top-k of the scores; least-recently-used
+// victims).
 #include <stdlib.h>
+
+#include <type_traits>
 
 #include "np_device.hpp"
 
@@ -115,247 +118,25 @@ __global__ __launch_bounds__(NT) void select_kernel(const float* __restrict__ sc
                            active_ids + (size_t)l * k, nullptr, scan);
 }
 
-// The rest of a radix select over `n` candidate keys gathered in LDS (all
-// nonzero and under `prefix`/`pmask`): 8-bit passes from bit `hi` down over
-// a histogram of 256 words at hist[0..], the bin placed by wave 0 (lane L
-// sums the 4 bins L-th from the top, a wave prefix sum finds the rem-th key).
-// Ends as block_select_largest's passes do: `prefix` the k-th key and `rem`
-// the keys equal to it still to take, or at a bin needed whole (prefix its
-// smallest key, rem no limit).  Every thread calls it.
-template <int NT>
-__device__ inline void select_candidates(const uint32_t* cand, uint32_t n, uint32_t* hist,
-                                         uint32_t* scan, uint32_t* res, int hi,
-                                         uint32_t& prefix, uint32_t& pmask, uint32_t& rem) {
-  constexpr int NW = NT / WAVE;
-  const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
-  while (hi >= 0) {
-    const int nbits = hi + 1 < 8 ? hi + 1 : 8;
-    const int shift = hi + 1 - nbits;
-    const uint32_t nb = 1u << nbits;
-    if ((uint32_t)tid < nb) hist[tid] = 0;
-    __syncthreads();
-    for (uint32_t c = tid; c < n; c += NT) {
-      const uint32_t kv = cand[c];
-      if ((kv & pmask) == prefix) atomicAdd(&hist[(kv >> shift) & (nb - 1)], 1u);
-    }
-    __syncthreads();
-    if (w == 0) {
-      uint32_t local = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int bin = (int)nb - 4 * lane - 1 - i;
-        if (bin >= 0) local += hist[bin];
-      }
-      const uint32_t incl = wave_incl_scan(local), above = incl - local;
-      if (above < rem && incl >= rem) {
-        uint32_t c = above;
-        for (int i = 0; i < 4; ++i) {
-          const int bin = (int)nb - 4 * lane - 1 - i;
-          const uint32_t h = hist[bin];
-          if (c + h >= rem) {
-            res[0] = (uint32_t)bin;
-            res[1] = rem - c;
-            res[2] = h == rem - c;
-            break;
-          }
-          c += h;
-        }
-      }
-    }
-    __syncthreads();
-    prefix |= res[0] << shift;
-    pmask |= (nb - 1) << shift;
-    rem = res[1];
-    hi = shift - 1;
-    const bool whole = res[2] != 0u && hi >= 0;
-    __syncthreads();  // hist and res are reused
-    if (whole) {
-      uint32_t kmn = 0xFFFFFFFFu;
-      for (uint32_t c = tid; c < n; c += NT) {
-        const uint32_t kv = cand[c];
-        if ((kv & pmask) == prefix && kv < kmn) kmn = kv;
-      }
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) {
-        const uint32_t o = __shfl_xor(kmn, off, WAVE);
-        kmn = o < kmn ? o : kmn;
-      }
-      if (lane == 0) scan[w] = kmn;
-      __syncthreads();
-      kmn = scan[0];
-      for (int i = 1; i < NW; ++i) kmn = scan[i] < kmn ? scan[i] : kmn;
-      __syncthreads();
-      prefix = kmn;
-      rem = 0xFFFFFFFFu;
-      return;
-    }
-  }
-}
-
-// The k largest score keys of one layer (ties to the smaller id), as
-// block_select_largest, starting from a hint: the previous token's k-th key
-// and a window half-width, kept per layer in the workspace.  Scores change
-// little from one token to the next, so the new k-th key usually lies in
-// [key - half, key + half].  One pass counts the keys above the window and
-// the keys in it; if the k-th key is inside (fewer than k above it, at least
-// k above its lower end) and the window holds at most SEL_HINT_CAP keys,
-// those keys go to LDS and the search finishes on them alone; otherwise the
-// full radix select runs.  Either way the result is the same, and the hint
-// is updated: the new k-th key, the window halved when it held many keys,
-// quadrupled when the k-th key fell outside it.  hist: 4096 words of LDS.
-constexpr uint32_t SEL_HINT_CAP = 4096 - 256;  // candidates kept after hist's first 256 words
-constexpr uint32_t SEL_HINT_HALF0 = 1u << 20;  // first window half-width (fp32 keys: 0.125 at 1.0)
-
-template <int NT>
-__device__ inline void select_largest_hinted(const uint32_t (&key)[1][32], uint32_t kk,
-                                             uint32_t (&sel)[1], uint32_t* hist, uint32_t* scan,
-                                             uint32_t* res, uint32_t* hint) {
-  constexpr int NW = NT / WAVE;
-  const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
-  const uint32_t hkey = hint ? hint[0] : 0u, hhalf = hint ? hint[1] : 0u;
-  const uint32_t lo = hkey > hhalf ? hkey - hhalf : 1u;
-  const uint32_t hi_w = hkey < 0xFFFFFFFFu - hhalf ? hkey + hhalf : 0xFFFFFFFFu;
-  // nonzero keys, keys above the window, keys in it
-  uint32_t nz = 0, above = 0, inside = 0;
-#pragma unroll
-  for (int b = 0; b < 32; ++b) {
-    const uint32_t kv = key[0][b];
-    nz += kv != 0u;
-    above += kv > hi_w;
-    inside += kv >= lo && kv <= hi_w;
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    nz += __shfl_xor(nz, off, WAVE);
-    above += __shfl_xor(above, off, WAVE);
-    inside += __shfl_xor(inside, off, WAVE);
-  }
-  if (lane == 0) {
-    scan[w] = nz;
-    scan[NW + w] = above;
-    scan[2 * NW + w] = inside;
-  }
-  __syncthreads();
-  nz = above = inside = 0;
-  for (int i = 0; i < NW; ++i) {
-    nz += scan[i];
-    above += scan[NW + i];
-    inside += scan[2 * NW + i];
-  }
-  __syncthreads();  // scan is reused below
-  const bool use = hkey != 0u && hhalf != 0u && kk < nz && above < kk && kk <= above + inside &&
-                   inside <= SEL_HINT_CAP;
-  uint32_t prefix = 0, rem = 0;
-  if (use) {
-    // the window's keys, in LDS after hist's first 256 words
-    uint32_t* cand = hist + 256;
-    uint32_t mine = 0;
-#pragma unroll
-    for (int b = 0; b < 32; ++b) mine += key[0][b] >= lo && key[0][b] <= hi_w;
-    uint32_t total;
-    uint32_t at = block_excl_scan<NT>(mine, scan, &total);
-#pragma unroll
-    for (int b = 0; b < 32; ++b)
-      if (key[0][b] >= lo && key[0][b] <= hi_w) cand[at++] = key[0][b];
-    // bits above the highest one in which lo and hi_w differ are common to
-    // every key of the window
-    const uint32_t diff = lo ^ hi_w;
-    const int hb = diff ? 31 - __builtin_clz(diff) : -1;
-    const uint32_t low = hb >= 0 ? (uint32_t)((2ull << hb) - 1ull) : 0u;
-    prefix = lo & ~low;
-    uint32_t pmask = ~low;
-    rem = kk - above;
-    __syncthreads();  // cand complete
-    select_candidates<NT>(cand, inside, hist, scan, res, hb, prefix, pmask, rem);
-    sel[0] = 0;
-  } else {
-    uint32_t s0[1];
-    block_select_largest<NT, 1>(key, kk, s0, hist, scan, res);
-    sel[0] = s0[0];
-  }
-  uint32_t kth = 0;  // the k-th key: the smallest selected one
-  if (use) {
-    // take every key above the k-th and the first `rem` equal ones in id order
-    uint32_t gt = 0, eq = 0;
-#pragma unroll
-    for (int b = 0; b < 32; ++b) {
-      gt |= (key[0][b] > prefix ? 1u : 0u) << b;
-      eq |= (key[0][b] == prefix ? 1u : 0u) << b;
-    }
-    uint32_t tot;
-    uint32_t before = block_excl_scan<NT>(__builtin_popcount(eq), scan, &tot);
-    while (eq && before < rem) {
-      const uint32_t lowbit = eq & (0u - eq);
-      gt |= lowbit;
-      eq ^= lowbit;
-      ++before;
-    }
-    sel[0] = gt;
-    kth = prefix;
-  } else if (hint && kk < nz) {
-    uint32_t mn = 0xFFFFFFFFu;
-#pragma unroll
-    for (int b = 0; b < 32; ++b)
-      if (((sel[0] >> b) & 1u) && key[0][b] < mn) mn = key[0][b];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const uint32_t o = __shfl_xor(mn, off, WAVE);
-      mn = o < mn ? o : mn;
-    }
-    if (lane == 0) scan[w] = mn;
-    __syncthreads();
-    kth = scan[0];
-    for (int i = 1; i < NW; ++i) kth = scan[i] < kth ? scan[i] : kth;
-    __syncthreads();
-  }
-  if (hint && tid == 0) {
-    uint32_t half = hhalf ? hhalf : SEL_HINT_HALF0;
-    if (use) {
-      if (inside > SEL_HINT_CAP / 4 && half > 1u) half >>= 1;
-    } else if (hkey != 0u && hhalf != 0u) {
-      half = half < (1u << 29) ? half << 2 : half;
-    }
-    hint[0] = kk < nz ? kth : 0u;
-    hint[1] = half;
-  }
-}
-
-// Limits of the fused selection + delta kernel (below): one id word per
-// thread at 512 threads, and the layer's slot_of and neuron_of in LDS.
-constexpr int SD_NT = 512;
-constexpr int SD_MAX_F = 32 * SD_NT;  // 16384
-constexpr int SD_MAX_C = 8192;
-constexpr int SD_MAX_K = 4096;
-constexpr int SD_PF = SD_MAX_F / SD_NT;  // slot_of loads per thread
-constexpr int SD_QF = SD_MAX_C / SD_NT;  // neuron_of loads per thread
-
-// The delta of one layer, run by all NT threads of its workgroup.  Thread t
-// owns: actives j in [t*JPT, t*JPT+JPT), id words [t*WPT, t*WPT+WPT) and slot
-// words [t*spt, t*spt+spt), so every list below comes out in ascending order
-// from a prefix sum in thread order.
-//   A: the layer's active ids (na of them, ascending); Pr, Qr: its slot_of
-//   and neuron_of as they were at entry, read from global memory or from
-//   copies in LDS; P, Q, U: the global slot_of, neuron_of and last_used,
-//   which the delta updates (Pr and Qr may be P and Q themselves: no
-//   restrict, and a thread reads an entry before any thread writes it).
-//   LDS_STATE: Pr and Qr are in LDS, where the free-slot and residency scans
-//   run as wave-wide passes (below); V4U: U's rows are 16-byte aligned (F a
-//   multiple of 4) and the victim keys are read as int4; PRE_U: they were
-//   read earlier, into upre (thread t: last_used of its id words).
+// The delta of one layer, run by all NT threads of its workgroup, for any
+// state, also an inconsistent one.  Thread t owns: actives j in [t*JPT,
+// t*JPT+JPT), id words [t*WPT, t*WPT+WPT) and slot words [t*spt, t*spt+spt), so
+// every list below comes out in ascending order from a prefix sum in thread
+// order.
+//   A: the layer's active ids (na of them, ascending); P, Q, U: its slot_of,
+//   neuron_of and last_used, read and updated in global memory (a thread
+//   reads an entry before any thread writes it).
 //   amask, rmask: >= ceil(F/32) words, smask: >= ceil(C/32) words of LDS;
-//   pool: >= na entries of LDS (it may share hist's storage: it is written
-//   only after the last use of hist).
+//   pool: >= na entries of LDS.
 // Every global gather of a phase is issued unconditionally (clamped index)
 // so that the phase costs one memory round trip, not one per element.
-template <int NT, int WPT, int JPT, bool LDS_STATE, bool V4U, bool PRE_U>
-__device__ __attribute__((always_inline)) inline void delta_layer(int l, int32_t token, const int32_t* A, int na, bool bad_count,
-                                   const int32_t* Pr, const int32_t* Qr, int32_t* P, int32_t* Q,
-                                   int32_t* U, const uint32_t (&upre)[WPT][32],
-                                   const np_delta_out& out, int F, int C, int k, int spt,
-                                   void* ws, uint32_t* amask, uint32_t* smask, uint32_t* rmask,
-                                   uint32_t* hist, int32_t* pool, uint32_t* scan,
-                                   uint32_t* res) {
-  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid / WAVE;
+template <int NT, int WPT, int JPT>
+__device__ inline void delta_layer(int l, int32_t token, const int32_t* A, int na, bool bad_count,
+                                   int32_t* P, int32_t* Q, int32_t* U, const np_delta_out& out,
+                                   int F, int C, int k, int spt, void* ws, uint32_t* amask,
+                                   uint32_t* smask, uint32_t* rmask, uint32_t* hist,
+                                   int32_t* pool, uint32_t* scan, uint32_t* res) {
+  const int tid = threadIdx.x;
   const int idwords = (F + 31) / 32, slotwords = (C + 31) / 32;
   const size_t lo = (size_t)l * k;
 
@@ -375,11 +156,11 @@ __device__ __attribute__((always_inline)) inline void delta_layer(int l, int32_t
     const bool ok = nj[q] >= 0 && nj[q] < F;  // else not a neuron id: counted as a miss
     if (tid * JPT + q < na) bad |= !ok;
     if (!ok) nj[q] = -1;
-    pj[q] = Pr[nj[q] >= 0 ? nj[q] : 0];
+    pj[q] = P[nj[q] >= 0 ? nj[q] : 0];
   }
   int qb[JPT];  // a hit's slot must hold it
 #pragma unroll
-  for (int q = 0; q < JPT; ++q) qb[q] = Qr[(pj[q] >= 0 && pj[q] < C) ? pj[q] : 0];
+  for (int q = 0; q < JPT; ++q) qb[q] = Q[(pj[q] >= 0 && pj[q] < C) ? pj[q] : 0];
 #pragma unroll
   for (int q = 0; q < JPT; ++q) {
     const int j = tid * JPT + q;
@@ -404,40 +185,12 @@ __device__ __attribute__((always_inline)) inline void delta_layer(int l, int32_t
   // 2. free slots and resident rows, and a consistency check of the slot
   //    map: a used slot's neuron must map back to it
   uint32_t nfree_local = 0;
-  if constexpr (LDS_STATE) {
-    // wave-wide passes over the slots: lane i takes slot base + i of 64
-    // consecutive ones, a ballot gives two words of free slots; a used
-    // slot's neuron must map back to it.
-    static_assert(NT == SD_NT, "the LDS path runs at SD_NT threads");
-    constexpr int NS = SD_MAX_C / SD_NT;
-    // the ballots stay in registers: lane 2j + h keeps word h of pass j and
-    // stores it after the loop.  A used slot whose neuron maps back to it
-    // marks that neuron resident.
-    uint32_t word = 0;
-    const int passes = (C - wv * WAVE + NT - 1) / NT;  // this wave's passes (<= NS)
-    for (int j = 0; j < passes; ++j) {
-      const int sl = wv * WAVE + j * NT + lane;
-      const int qv = Qr[min(sl, C - 1)];
-      const int back = Pr[(uint32_t)qv < (uint32_t)F ? qv : 0];
-      const bool in = sl < C, used = in & (qv != -1);
-      const bool pair = ((uint32_t)qv < (uint32_t)F) & (back == sl);
-      bad |= used & !pair;
-      if (used & pair) atomicOr(&rmask[qv >> 5], 1u << (qv & 31));
-      const uint64_t fm = __ballot(in & (qv == -1));
-      word = lane == 2 * j ? (uint32_t)fm : (lane == 2 * j + 1 ? (uint32_t)(fm >> 32) : word);
-      nfree_local += lane == 0 ? __popcll(fm) : 0;
-    }
-    {
-      const int wi = 2 * wv + (NT / 32) * (lane / 2) + (lane & 1);
-      if (lane < 2 * NS && wi < slotwords) smask[wi] = word;
-    }
-  } else
   for (int q = 0; q < spt; ++q) {
     const int sw = tid * spt + q;
     if (sw >= slotwords) break;
     int qn[32];
 #pragma unroll
-    for (int b = 0; b < 32; ++b) qn[b] = Qr[min(32 * sw + b, C - 1)];
+    for (int b = 0; b < 32; ++b) qn[b] = Q[min(32 * sw + b, C - 1)];
     uint32_t bits = 0;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {  // halves: 16 back-gathers in flight
@@ -445,7 +198,7 @@ __device__ __attribute__((always_inline)) inline void delta_layer(int l, int32_t
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int qv = qn[16 * h + i];
-        back[i] = Pr[(qv >= 0 && qv < F) ? qv : 0];
+        back[i] = P[(qv >= 0 && qv < F) ? qv : 0];
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -480,24 +233,8 @@ __device__ __attribute__((always_inline)) inline void delta_layer(int l, int32_t
 #pragma unroll
       for (int w = 0; w < WPT; ++w) {
         const int word = tid * WPT + w;
-        if constexpr (PRE_U) {
 #pragma unroll
-          for (int b = 0; b < 32; ++b) key[w][b] = upre[w][b];
-        } else if constexpr (V4U) {
-          const int4* u4 = reinterpret_cast<const int4*>(U);
-          const int last = F / 4 - 1;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const int4 q = u4[min(8 * word + i, last)];
-            key[w][4 * i] = (uint32_t)q.x;
-            key[w][4 * i + 1] = (uint32_t)q.y;
-            key[w][4 * i + 2] = (uint32_t)q.z;
-            key[w][4 * i + 3] = (uint32_t)q.w;
-          }
-        } else {
-#pragma unroll
-          for (int b = 0; b < 32; ++b) key[w][b] = (uint32_t)U[min(32 * word + b, F - 1)];
-        }
+        for (int b = 0; b < 32; ++b) key[w][b] = (uint32_t)U[min(32 * word + b, F - 1)];
         // resident, not active, and inside the layer (rmask has no bits past F)
         const uint32_t cm = word < idwords ? (rmask[word] & ~amask[word]) : 0u;
 #pragma unroll
@@ -519,28 +256,9 @@ __device__ __attribute__((always_inline)) inline void delta_layer(int l, int32_t
     for (int w = 0; w < WPT; ++w) {
       if (!vsel[w]) continue;
       const int word = tid * WPT + w;
-      if constexpr (LDS_STATE) {  // LDS: only the victims' entries, one by one
-        uint32_t bits = vsel[w];
-        while (bits) {
-          const int b = __builtin_ctz(bits);
-          bits &= bits - 1;
-          const int n = 32 * word + b, old = Pr[n];
-          if (old < 0 || old >= C || vpos >= (uint32_t)k) {  // only with a corrupted state
-            bad = 1;
-            continue;
-          }
-          out.ev_ids[lo + vpos] = n;
-          out.ev_slots[lo + vpos] = old;
-          ++vpos;
-          atomicOr(&smask[old >> 5], 1u << (old & 31));
-          Q[old] = -1;
-          P[n] = -1;
-        }
-        continue;
-      }
       int pn[32];
 #pragma unroll
-      for (int b = 0; b < 32; ++b) pn[b] = Pr[min(32 * word + b, F - 1)];
+      for (int b = 0; b < 32; ++b) pn[b] = P[min(32 * word + b, F - 1)];
 #pragma unroll
       for (int b = 0; b < 32; ++b) {
         if (!((vsel[w] >> b) & 1u)) continue;
@@ -622,7 +340,679 @@ __device__ __attribute__((always_inline)) inline void delta_layer(int l, int32_t
   }
 }
 
-// np_delta: one workgroup per layer, the state read from global memory.
+// ---------------------------------------------------------------------------
+// The selection and the delta with the layer's slot map in LDS: F <= 32768,
+// C <= 16384 (slots and -1 in 16 bits), k <= 8192, 1024 threads.
+//
+// Bound by latency: one workgroup per layer, so the chain of barriers, LDS
+// round trips and wave-wide scans is the time (the bytes, 0.15 to 0.5 MB a
+// layer, take a fraction of it).  So every phase is cut to one barrier where
+// it can be: prefix sums in DPP with one exchange of wave totals, histograms
+// that every wave reads by itself (a coarse and a fine level, one bin a lane)
+// instead of a workgroup scan, masks built with ballots from the values that
+// are loaded anyway instead of LDS atomics, and the consistency of the slot map
+// checked once, which frees every later step of its checks: an inconsistent
+// layer takes delta_checked.  7B, per token: 23.3 us with 512
+// threads of 32 ids and about 45 barriers; 70B: 22.3 + 21.2 us in two kernels
+// that read the state from memory.  The figures now are at the launch rule.
+// ---------------------------------------------------------------------------
+constexpr int SD_NT = 1024;
+constexpr int SD_NW = SD_NT / WAVE;
+constexpr int SD_MAX_F = 32 * SD_NT;  // 32768
+constexpr int SD_MAX_C = 16 * SD_NT;  // 16384
+constexpr int SD_MAX_K = 8192;
+constexpr int SD_BINS = 2048;         // fine bins of a histogram
+constexpr int SD_COARSE = 64;         // coarse bins: SD_BINS / 64 fine ones each
+constexpr int SD_CAND = 64;           // keys of a bin resolved by one wave
+
+// LDS of the fast path (F ids of KPT per thread)
+template <int KPT>
+struct SdLds {
+  int16_t slot[KPT * SD_NT];            // slot_of at entry
+  uint16_t pool[SD_MAX_K];              // slots for the incoming rows, ascending
+  uint32_t amask[KPT * SD_NT / 32], rmask[KPT * SD_NT / 32];  // active, resident
+  uint32_t smask[SD_MAX_F / 32];        // free slots, then also the victims'
+  uint32_t hist[SD_BINS], coarse[SD_COARSE];
+  uint32_t vhist[SD_BINS], vcoarse[SD_COARSE];  // the victims'
+  uint32_t cand[SD_CAND], scan[8][SD_NW];
+  uint32_t above, ncand, vmax, used, valid, nfree, bad;
+};
+// LDS of delta_checked, when the slot map is inconsistent
+struct SdChecked {
+  uint32_t amask[SD_MAX_F / 32], smask[SD_MAX_F / 32], rmask[SD_MAX_F / 32], hist[256];
+  int32_t pool[SD_MAX_K], held[SD_MAX_K];
+  uint32_t scan[SD_NW];
+};
+template <int KPT>
+union SdShared {
+  SdLds<KPT> f;
+  SdChecked g;
+};
+
+// The bin of a histogram (fine, coarse: filled alike) that holds the rem-th
+// key counted from bin 0 up, and the keys before it; every wave by itself.
+// Returns false when the histogram holds fewer than rem.
+__device__ inline bool find_bin(const uint32_t* fine, const uint32_t* coarse, uint32_t rem,
+                                uint32_t* bin, uint32_t* before, uint32_t* count) {
+  constexpr int PER = SD_BINS / SD_COARSE;
+  const int lane = threadIdx.x & (WAVE - 1);
+  const uint32_t c = wave_incl_scan(coarse[lane]);
+  const uint64_t hit = __ballot(c >= rem);
+  if (!hit) return false;
+  const int cb = __builtin_ctzll(hit);
+  const uint32_t cbefore = cb > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)c, cb > 0 ? cb - 1 : 0) : 0u;
+  const uint32_t v = lane < PER ? fine[cb * PER + lane] : 0u;
+  const uint32_t f = wave_incl_scan(v) + cbefore;
+  const int fb = __builtin_ctzll(__ballot(f >= rem));
+  *count = (uint32_t)__builtin_amdgcn_readlane((int)v, fb);
+  *before = (uint32_t)__builtin_amdgcn_readlane((int)f, fb) - *count;
+  *bin = (uint32_t)(cb * PER + fb);
+  return true;
+}
+
+// bits b of words that two threads share (KPT = 16) or own (32): the word of
+// ids 32 w .. 32 w + 31 in the thread that holds its low bits
+template <int KPT>
+__device__ inline uint32_t whole_word(uint32_t bits) {
+  if constexpr (KPT == 32) return bits;
+  const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)bits, DPP_XOR1, 0xF, 0xF, true);
+  return bits | (other << 16);  // of use in even lanes
+}
+
+// The k largest keys of the layer (ties to the smaller ids), starting from a
+// hint kept per layer in the workspace: the previous token's k-th key and a
+// window half-width.  Scores change little from one token to the next, so the
+// new k-th key usually lies in [key - half, key + half].  One pass counts the
+// keys above the window and puts those inside into a histogram; every wave
+// finds the k-th key's bin, and the few keys of that bin decide.  Whatever the
+// hint holds, the result is the same: when the k-th key is outside the window
+// or its bin holds more than SD_CAND keys, the full radix select runs.  The
+// hint is updated: the new k-th key, the window halved when it held many keys,
+// quadrupled when the k-th key fell outside it.
+constexpr uint32_t SEL_HINT_MANY = 960;
+constexpr uint32_t SEL_HINT_HALF0 = 1u << 20;  // first window half-width (fp32 keys: 0.125 at 1.0)
+
+template <int KPT>
+__device__ inline uint32_t select_hinted(const uint32_t (&key)[1][KPT], uint32_t kk,
+                                         SdLds<KPT>& s, uint32_t* work, uint32_t* hint) {
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+  const uint32_t hkey = hint ? hint[0] : 0u, half = hint ? hint[1] : 0u;
+  const uint32_t lo = hkey > half ? hkey - half : 1u;
+  const uint32_t hi = hkey < 0xFFFFFFFFu - half ? hkey + half : 0xFFFFFFFFu;
+  const bool window = hkey != 0u && half != 0u;
+  bool use = false;
+  uint32_t kth = 0, eq_take = 0, eq_all = 0, inside = 0;
+  if (window) {
+    const uint32_t width = hi - lo;  // bins of 2^shift keys, from the top
+    const int bits = width ? 32 - __builtin_clz(width) : 0;
+    const int shift = bits > 11 ? bits - 11 : 0;
+    uint32_t above = 0;
+#pragma unroll
+    for (int b = 0; b < KPT; ++b) {
+      const uint32_t d = hi - key[0][b];  // keys above hi wrap past width
+      above += key[0][b] > hi;
+      if (key[0][b] <= hi && d <= width) {
+        atomicAdd(&s.hist[d >> shift], 1u);
+        atomicAdd(&s.coarse[(d >> shift) / (SD_BINS / SD_COARSE)], 1u);
+      }
+    }
+    above = wave_total(above);
+    if (lane == 0 && above) atomicAdd(&s.above, above);
+    lds_barrier();
+    above = s.above;
+    uint32_t bin = 0, before = 0, count = 0;
+    use = above < kk && find_bin(s.hist, s.coarse, kk - above, &bin, &before, &count) &&
+          count <= SD_CAND;
+    if (use) {  // the keys of the bin, in any order
+      const uint32_t rem = kk - above - before;
+#pragma unroll
+      for (int b = 0; b < KPT; ++b) {
+        const uint32_t d = hi - key[0][b];
+        if (key[0][b] <= hi && d <= width && (d >> shift) == bin)
+          s.cand[atomicAdd(&s.ncand, 1u)] = key[0][b];
+      }
+      lds_barrier();
+      const uint32_t mine = (uint32_t)lane < count ? s.cand[lane] : 0u;
+      uint32_t gt = 0, eq = 0;  // keys of the bin above this lane's, equal to it
+      for (uint32_t j = 0; j < count; ++j) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)j);
+        gt += o > mine;
+        eq += o == mine;
+      }
+      const int at = __builtin_ctzll(__ballot((uint32_t)lane < count && gt < rem && rem <= gt + eq));
+      kth = (uint32_t)__builtin_amdgcn_readlane((int)mine, at);
+      eq_take = rem - (uint32_t)__builtin_amdgcn_readlane((int)gt, at);
+      eq_all = (uint32_t)__builtin_amdgcn_readlane((int)eq, at);
+      inside = wave_total(s.coarse[lane]);
+    }
+  }
+  uint32_t sel[1];
+  if (use) {
+    uint32_t gt = 0, eq = 0;
+#pragma unroll
+    for (int b = 0; b < KPT; ++b) {
+      gt |= (key[0][b] > kth ? 1u : 0u) << b;
+      eq |= (key[0][b] == kth ? 1u : 0u) << b;
+    }
+    if (eq_take == eq_all) {
+      sel[0] = gt | eq;
+    } else {  // the first eq_take of the equal keys, in id order
+      uint32_t tot;
+      uint32_t n = block_excl_scan_once<SD_NT>(__builtin_popcount(eq), s.scan[0], &tot);
+      while (eq && n < eq_take) {
+        gt |= eq & (0u - eq);
+        eq &= eq - 1;
+        ++n;
+      }
+      sel[0] = gt;
+    }
+  } else {
+    __syncthreads();  // every wave is done with the window's histogram
+    block_select_largest<SD_NT, 1>(key, kk, sel, work, work + 4096, work + 4096 + 3 * SD_NW + 1);
+    if (hint) {  // the k-th key: the smallest selected one
+      uint32_t mx = 0;
+#pragma unroll
+      for (int b = 0; b < KPT; ++b)
+        if (((sel[0] >> b) & 1u) && ~key[0][b] > mx) mx = ~key[0][b];
+      mx = wave_max(mx);
+      if (lane == 0) s.scan[0][tid / WAVE] = mx;
+      __syncthreads();
+      for (int i = 0; i < SD_NW; ++i) mx = s.scan[0][i] > mx ? s.scan[0][i] : mx;
+      kth = ~mx;  // 0 when a NaN or padding key was taken
+    }
+  }
+  if (hint && tid == 0) {
+    uint32_t h = half ? half : SEL_HINT_HALF0;
+    if (use) {
+      if (inside > SEL_HINT_MANY && h > 1u) h >>= 1;
+    } else if (window) {
+      h = h < (1u << 29) ? h << 2 : h;
+    }
+    hint[0] = kth;
+    hint[1] = h;
+  }
+  return sel[0];
+}
+
+// slot_of of one layer to LDS, with the resident bits and the counts of valid
+// entries; an entry outside {-1} and [0, C) sets bad.  V4: the rows of the
+// layer are 16-byte aligned (F a multiple of 4).
+template <int KPT, bool V4>
+struct SlotLoads {
+  int4 v4[V4 ? KPT / 4 : 1];
+  int v1[V4 ? 1 : KPT];
+  __device__ inline void load(const int32_t* P, int F) {
+    const int tid = threadIdx.x;
+    if constexpr (V4) {
+#pragma unroll
+      for (int i = 0; i < KPT / 4; ++i)
+        v4[i] = reinterpret_cast<const int4*>(P)[min(tid + SD_NT * i, F / 4 - 1)];
+    } else {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) v1[i] = P[min(tid + SD_NT * i, F - 1)];
+    }
+  }
+  __device__ inline void store(SdLds<KPT>& s, int F, int C) {
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    uint32_t valid = 0;
+    bool bad = false;
+    if constexpr (V4) {
+#pragma unroll
+      for (int i = 0; i < KPT / 4; ++i) {
+        const int g = tid + SD_NT * i;
+        const bool in = 4 * g < F;
+        const int e[4] = {v4[i].x, v4[i].y, v4[i].z, v4[i].w};
+        uint32_t m = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          bad |= in && (e[c] < -1 || e[c] >= C);
+          m |= (in && e[c] >= 0 ? 1u : 0u) << c;
+        }
+        valid += __builtin_popcount(m);
+        *(uint2*)&s.slot[4 * g] = make_uint2((uint32_t)(e[0] & 0xFFFF) | ((uint32_t)e[1] << 16),
+                                             (uint32_t)(e[2] & 0xFFFF) | ((uint32_t)e[3] << 16));
+        m <<= 4 * (lane & 7);  // eight lanes hold a word's nibbles
+        m |= (uint32_t)__builtin_amdgcn_mov_dpp((int)m, DPP_XOR1, 0xF, 0xF, true);
+        m |= (uint32_t)__builtin_amdgcn_mov_dpp((int)m, DPP_XOR2, 0xF, 0xF, true);
+        m |= (uint32_t)__builtin_amdgcn_mov_dpp((int)m, DPP_XOR7, 0xF, 0xF, true);
+        if ((lane & 7) == 0) s.rmask[g >> 3] = m;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) {
+        const int n = tid + SD_NT * i;
+        const bool in = n < F;
+        bad |= in && (v1[i] < -1 || v1[i] >= C);
+        const uint64_t m = __ballot(in && v1[i] >= 0);
+        valid += lane == 0 ? (uint32_t)__popcll(m) : 0u;
+        s.slot[n] = (int16_t)v1[i];
+        if (lane == 0) *(uint2*)&s.rmask[n >> 5] = make_uint2((uint32_t)m, (uint32_t)(m >> 32));
+      }
+    }
+    valid = wave_total(valid);
+    if (lane == 0 && valid) atomicAdd(&s.valid, valid);
+    if (bad) s.bad = 1u;
+  }
+};
+
+// Clears the counters and histograms; a barrier must follow before their use.
+template <int KPT>
+__device__ inline void sd_clear(SdLds<KPT>& s) {
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < SD_BINS / SD_NT; ++i) s.hist[tid + SD_NT * i] = s.vhist[tid + SD_NT * i] = 0u;
+  if (tid < SD_COARSE) s.coarse[tid] = s.vcoarse[tid] = 0u;
+  if (tid == 0) s.above = s.ncand = s.vmax = s.used = s.valid = s.nfree = s.bad = 0u;
+}
+
+// The delta of one layer with a consistent slot map in LDS.  qv: this
+// thread's neuron_of entries (slot tid + 1024 i); ids: the layer's active ids
+// in LDS (16 bits, ascending); s.slot, s.amask, s.rmask, s.valid and s.bad
+// complete behind a barrier.  Returns false, having written nothing, when the
+// slot map turns out inconsistent.
+template <int KPT, int CPT, int JPT, bool V4>
+__device__ inline bool delta_fast(int l, int32_t token, const uint16_t* ids, int na,
+                                  const int (&qv)[CPT], int32_t* P, int32_t* Q, int32_t* U,
+                                  const np_delta_out& out, int F, int C, int k, SdLds<KPT>& s,
+                                  uint32_t* work) {
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+  const size_t lo = (size_t)l * k;
+  // the ids' last_used, for the victims (in flight meanwhile)
+  uint32_t key[1][KPT];
+  if (KPT * tid < F) {
+    if constexpr (V4) {
+      const int last = F / 4 - 1;
+#pragma unroll
+      for (int i = 0; i < KPT / 4; ++i) {
+        const int4 q = reinterpret_cast<const int4*>(U)[min(KPT / 4 * tid + i, last)];
+        key[0][4 * i] = (uint32_t)q.x;
+        key[0][4 * i + 1] = (uint32_t)q.y;
+        key[0][4 * i + 2] = (uint32_t)q.z;
+        key[0][4 * i + 3] = (uint32_t)q.w;
+      }
+    } else {
+#pragma unroll
+      for (int b = 0; b < KPT; ++b) key[0][b] = (uint32_t)U[min(KPT * tid + b, F - 1)];
+    }
+  } else {
+#pragma unroll
+    for (int b = 0; b < KPT; ++b) key[0][b] = 0u;
+  }
+  // 1. free slots, and the consistency of the map: a used slot's neuron must
+  //    map back to it, and no more neurons may hold slots than slots are used
+  {
+    int back[CPT];
+#pragma unroll
+    for (int i = 0; i < CPT; ++i)
+      back[i] = (uint32_t)qv[i] < (uint32_t)F ? (int)s.slot[qv[i]] : -2;
+    uint32_t nfree = 0, used = 0;
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+      const int sl = tid + SD_NT * i;
+      const bool in = sl < C, fr = in && qv[i] == -1, us = in && qv[i] != -1;
+      bad |= us && back[i] != sl;
+      const uint64_t fm = __ballot(fr);
+      nfree += (uint32_t)__popcll(fm);
+      used += (uint32_t)__popcll(__ballot(us));
+      if (lane == 0 && SD_NT * i < C)
+        *(uint2*)&s.smask[sl >> 5] = make_uint2((uint32_t)fm, (uint32_t)(fm >> 32));
+    }
+    if (lane == 0) {
+      if (nfree) atomicAdd(&s.nfree, nfree);
+      if (used) atomicAdd(&s.used, used);
+    }
+    if (bad) s.bad = 1u;
+  }
+  // 2. hits and incoming rows, in active-list order
+  int nj[JPT], pj[JPT];
+  uint32_t hi_cnt = 0;  // hits | incoming << 16
+#pragma unroll
+  for (int q = 0; q < JPT; ++q) {
+    const int j = tid * JPT + q;
+    nj[q] = ids[min(j, na > 0 ? na - 1 : 0)];
+    pj[q] = s.slot[na > 0 ? nj[q] : 0];
+    if (j < na) hi_cnt += pj[q] >= 0 ? 1u : 0x10000u;
+  }
+  uint32_t tot;
+  const uint32_t before = block_excl_scan_once<SD_NT>(hi_cnt, s.scan[1], &tot);
+  if (s.bad || s.used != s.valid) return false;  // uniform
+  const uint32_t nH = tot & 0xFFFFu, nI = tot >> 16;
+  const uint32_t m = nI > s.nfree ? nI - s.nfree : 0u;
+  // 3. victims: the m resident, non-active rows with the smallest (last_used,
+  //    id) -- the largest keys ~last_used, ties to lower ids; their slots join
+  //    the free ones
+  if (m > 0) {
+    const int word = KPT == 32 ? tid : tid >> 1;
+    uint32_t cm = KPT * tid < F ? s.rmask[word] & ~s.amask[word] : 0u;
+    if constexpr (KPT == 16) cm = (cm >> (16 * (tid & 1))) & 0xFFFFu;
+    uint32_t mx = 0;
+    bool odd = false;
+#pragma unroll
+    for (int b = 0; b < KPT; ++b) {
+      key[0][b] = ((cm >> b) & 1u) ? ~key[0][b] : 0u;
+      odd |= ((cm >> b) & 1u) && key[0][b] == 0u;  // resident and never used
+      mx = key[0][b] > mx ? key[0][b] : mx;
+    }
+    mx = wave_max(mx);
+    if (lane == 0 && mx) atomicMax(&s.vmax, mx);
+    if (odd) s.bad = 1u;
+    lds_barrier();
+    if (s.bad) return false;  // uniform; nothing is written yet
+    mx = s.vmax;
+    // ages from the oldest candidate's: bin 0 is the oldest token
+#pragma unroll
+    for (int b = 0; b < KPT; ++b) {
+      const uint32_t d = mx - key[0][b];
+      if (key[0][b] != 0u && d < (uint32_t)SD_BINS) {
+        atomicAdd(&s.vhist[d], 1u);
+        atomicAdd(&s.vcoarse[d / (SD_BINS / SD_COARSE)], 1u);
+      }
+    }
+    lds_barrier();
+    uint32_t vsel, vpos, bin, bef, cnt;
+    if (find_bin(s.vhist, s.vcoarse, m, &bin, &bef, &cnt)) {
+      uint32_t older = 0, eq = 0;
+#pragma unroll
+      for (int b = 0; b < KPT; ++b) {
+        const uint32_t d = mx - key[0][b];
+        older |= (key[0][b] != 0u && d < bin ? 1u : 0u) << b;
+        eq |= (key[0][b] != 0u && d == bin ? 1u : 0u) << b;
+      }
+      // one prefix sum places both: all older ones, the first m - bef equal
+      const uint32_t take = m - bef;
+      uint32_t t2;
+      const uint32_t pre = block_excl_scan_once<SD_NT>(
+          (uint32_t)__builtin_popcount(older) | ((uint32_t)__builtin_popcount(eq) << 16), s.scan[2],
+          &t2);
+      uint32_t ne = pre >> 16;
+      vpos = (pre & 0xFFFFu) + (ne < take ? ne : take);
+      vsel = older;
+      while (eq && ne < take) {
+        vsel |= eq & (0u - eq);
+        eq &= eq - 1;
+        ++ne;
+      }
+    } else {  // the oldest m span more than SD_BINS tokens
+      uint32_t sel[1];
+      __syncthreads();
+      block_select_largest<SD_NT, 1>(key, m, sel, work, work + 4096, work + 4096 + 3 * SD_NW + 1);
+      vsel = sel[0];
+      uint32_t t2;
+      vpos = block_excl_scan_once<SD_NT>(__builtin_popcount(vsel), s.scan[2], &t2);
+    }
+    while (vsel) {
+      const int n = KPT * tid + __builtin_ctz(vsel), old = s.slot[n];
+      vsel &= vsel - 1;
+      out.ev_ids[lo + vpos] = n;
+      out.ev_slots[lo + vpos] = old;
+      ++vpos;
+      atomicOr(&s.smask[old >> 5], 1u << (old & 31));
+      Q[old] = -1;
+      P[n] = -1;
+    }
+    lds_barrier();
+  }
+  // 4. the slot pool in ascending order: its first nI slots go to the
+  //    incoming rows (ascending ids)
+  {
+    uint32_t bits = 32 * tid < C ? s.smask[tid] : 0u;
+    uint32_t st;
+    uint32_t pos = block_excl_scan_once<SD_NT>(__builtin_popcount(bits), s.scan[3], &st);
+    while (bits && pos < nI) {
+      const int sl = 32 * tid + __builtin_ctz(bits);
+      bits &= bits - 1;
+      out.in_slots[lo + pos] = sl;
+      s.pool[pos] = (uint16_t)sl;
+      ++pos;
+    }
+  }
+  __syncthreads();  // the victims' stores to P and Q come before the incoming rows'
+  // 5. incoming rows take their slots; lists and last_used
+  uint32_t hb = before & 0xFFFFu, ib = before >> 16;
+#pragma unroll
+  for (int q = 0; q < JPT; ++q) {
+    const int j = tid * JPT + q;
+    if (j < na) {
+      const int n = nj[q];
+      int slot = pj[q];
+      if (slot >= 0) {
+        out.hit_ids[lo + hb++] = n;
+      } else {
+        slot = s.pool[ib];
+        out.in_ids[lo + ib++] = n;
+        P[n] = slot;
+        Q[slot] = n;
+      }
+      U[n] = token;
+      out.active_slots[lo + j] = slot;
+    }
+  }
+  if (tid == 0) {
+    out.counts[(size_t)l * 4 + 0] = (int32_t)nI;
+    out.counts[(size_t)l * 4 + 1] = (int32_t)nH;
+    out.counts[(size_t)l * 4 + 2] = (int32_t)m;
+    out.counts[(size_t)l * 4 + 3] = (int32_t)(nI - m);
+  }
+  return true;
+}
+
+// The delta of one layer whose slot map delta_fast found inconsistent (or
+// whose ids are not ascending neuron ids): delta_layer's steps and results,
+// entry by entry from memory with every check, in few registers so that it
+// costs the fast path none.  Thread t owns id word t, slot word t and actives
+// [t*jpt, t*jpt+jpt).
+__device__ inline void delta_checked(int l, int32_t token, const int32_t* A, int na,
+                                     bool bad_count, int32_t* P, int32_t* Q, int32_t* U,
+                                     const np_delta_out& out, int F, int C, int k, void* ws,
+                                     SdChecked& g) {
+  const int tid = threadIdx.x, jpt = (k + SD_NT - 1) / SD_NT;
+  const size_t lo = (size_t)l * k;
+  const int j0 = min(tid * jpt, na), j1 = min(tid * jpt + jpt, na);
+  __syncthreads();  // every thread is done with the LDS of the fast path
+  g.amask[tid] = g.rmask[tid] = 0u;
+  __syncthreads();
+  uint32_t cnt = 0, bad = bad_count && tid == 0;
+#pragma unroll 1
+  for (int j = j0; j < j1; ++j) {  // hits and incoming rows
+    const int n = A[j];
+    int p = -1;
+    if (n >= 0 && n < F) {
+      atomicOr(&g.amask[n >> 5], 1u << (n & 31));
+      p = P[n];
+      if (p >= C || (p >= 0 && Q[p] != n)) {
+        bad = 1;
+        p = -1;
+      }
+    } else {
+      bad = 1;
+    }
+    if (p < 0) p = -1;
+    g.held[j] = p;
+    cnt += p >= 0 ? 1u : 0x10000u;
+  }
+  uint32_t tot;
+  const uint32_t before = block_excl_scan<SD_NT>(cnt, g.scan, &tot);
+  const uint32_t nH = tot & 0xFFFFu, nI = tot >> 16;
+  uint32_t bits = 0;
+#pragma unroll 1
+  for (int sl = 32 * tid; sl < min(32 * tid + 32, C); ++sl) {  // free slots, resident rows
+    const int q = Q[sl];
+    if (q == -1) bits |= 1u << (sl & 31);
+    else if (q < 0 || q >= F || P[q] != sl) bad = 1;
+    else atomicOr(&g.rmask[q >> 5], 1u << (q & 31));
+  }
+  g.smask[tid] = bits;
+  uint32_t nfree;
+  (void)block_excl_scan<SD_NT>(__builtin_popcount(bits), g.scan, &nfree);
+  const uint32_t m = nI > nfree ? nI - nfree : 0u;
+  if (m > 0) {  // the m largest keys ~last_used of the resident, non-active rows
+    const uint32_t cm = g.rmask[tid] & ~g.amask[tid];
+    auto key = [&](int b) { return ((cm >> b) & 1u) ? ~(uint32_t)U[32 * tid + b] : 0u; };
+    uint32_t nz = 0;
+#pragma unroll 1
+    for (int b = 0; b < 32; ++b) nz += key(b) != 0u;
+    (void)block_excl_scan<SD_NT>(nz, g.scan, &nz);
+    uint32_t prefix = 0, pmask = 0, rem = m >= nz ? m - nz : m;
+    if (m < nz) {
+#pragma unroll 1
+      for (int shift = 24; shift >= 0; shift -= 8) {
+        if (tid < 256) g.hist[tid] = 0u;
+        __syncthreads();
+#pragma unroll 1
+        for (int b = 0; b < 32; ++b) {
+          const uint32_t kv = key(b);
+          if (kv != 0u && (kv & pmask) == prefix) atomicAdd(&g.hist[(kv >> shift) & 255u], 1u);
+        }
+        __syncthreads();
+        uint32_t bin = 255;
+        while (g.hist[bin] < rem) rem -= g.hist[bin--];
+        prefix |= bin << shift;
+        pmask |= 255u << shift;
+        __syncthreads();
+      }
+    }
+    uint32_t vsel = 0, eq = 0;
+#pragma unroll 1
+    for (int b = 0; b < 32; ++b) {
+      const uint32_t kv = key(b);
+      vsel |= (kv > prefix ? 1u : 0u) << b;
+      eq |= (kv == prefix ? 1u : 0u) << b;
+    }
+    uint32_t t2;
+    uint32_t ne = block_excl_scan<SD_NT>(__builtin_popcount(eq), g.scan, &t2);
+    while (eq && ne < rem) {
+      vsel |= eq & (0u - eq);
+      eq &= eq - 1;
+      ++ne;
+    }
+    uint32_t vpos = block_excl_scan<SD_NT>(__builtin_popcount(vsel), g.scan, &t2);
+#pragma unroll 1
+    while (vsel) {
+      const int n = 32 * tid + __builtin_ctz(vsel), old = P[min(n, F - 1)];
+      vsel &= vsel - 1;
+      if (old < 0 || old >= C || vpos >= (uint32_t)k) {
+        bad = 1;
+        continue;
+      }
+      out.ev_ids[lo + vpos] = n;
+      out.ev_slots[lo + vpos] = old;
+      ++vpos;
+      atomicOr(&g.smask[old >> 5], 1u << (old & 31));
+      Q[old] = -1;
+      P[n] = -1;
+    }
+  }
+  __syncthreads();
+  bits = g.smask[tid];
+  uint32_t st;
+  uint32_t pos = block_excl_scan<SD_NT>(__builtin_popcount(bits), g.scan, &st);
+  const uint32_t given = st < nI ? st : nI;  // slots actually handed out
+#pragma unroll 1
+  while (bits && pos < nI) {
+    const int sl = 32 * tid + __builtin_ctz(bits);
+    bits &= bits - 1;
+    out.in_slots[lo + pos] = sl;
+    g.pool[pos] = sl;
+    ++pos;
+  }
+  __syncthreads();
+  uint32_t hb = before & 0xFFFFu, ib = before >> 16;
+#pragma unroll 1
+  for (int j = j0; j < j1; ++j) {
+    int n = A[j], slot = g.held[j];
+    if (n < 0 || n >= F) n = -1;
+    if (slot >= 0) {
+      out.hit_ids[lo + hb++] = n;
+    } else {
+      slot = ib < given ? g.pool[ib] : -1;
+      out.in_ids[lo + ib++] = n;
+      if (n >= 0 && slot >= 0 && slot < C) {
+        P[n] = slot;
+        Q[slot] = n;
+      } else {
+        bad = 1;
+        slot = -1;
+      }
+    }
+    if (n >= 0) U[n] = token;
+    out.active_slots[lo + j] = slot;
+  }
+  if (bad) raise_error(ws, NP_DEVERR_STATE);
+  if (tid == 0) {
+    out.counts[(size_t)l * 4 + 0] = (int32_t)nI;
+    out.counts[(size_t)l * 4 + 1] = (int32_t)nH;
+    out.counts[(size_t)l * 4 + 2] = (int32_t)m;
+    out.counts[(size_t)l * 4 + 3] = (int32_t)(nI - m);
+  }
+}
+
+// np_delta and np_delta_n with the slot map in LDS.  Ids that are not
+// strictly ascending neuron ids go to the general delta, as does an
+// inconsistent slot map.
+template <int KPT, int CPT, int JPT, bool V4>
+__global__ __launch_bounds__(SD_NT) void delta_lds_kernel(
+    int32_t token, const int32_t* __restrict__ active_ids, int32_t* __restrict__ slot_of,
+    int32_t* __restrict__ neuron_of, int32_t* __restrict__ last_used, np_delta_out out, int F,
+    int C, int k, void* ws, const int32_t* __restrict__ counts) {
+  __shared__ __attribute__((aligned(16))) SdShared<KPT> sh;
+  __shared__ uint16_t ids_s[SD_MAX_K];
+  __shared__ uint32_t work[4096 + 3 * SD_NW + 1 + 4];
+  SdLds<KPT>& s = sh.f;
+  const int l = blockIdx.x, tid = threadIdx.x;
+  if (token == NP_TOKEN_AUTO) token = *(const int32_t*)((const char*)ws + WS_TOKEN);
+  int32_t* P = slot_of + (size_t)l * F;
+  int32_t* Q = neuron_of + (size_t)l * C;
+  int32_t* U = last_used + (size_t)l * F;
+  const int32_t* A = active_ids + (size_t)l * k;
+  SlotLoads<KPT, V4> p;
+  p.load(P, F);
+  int na = k;  // active neurons of this layer: k, or a device count in [0, k]
+  bool bad_count = false;
+  if (counts) {
+    na = counts[l];
+    if (na < 0 || na > k) {
+      bad_count = true;
+      na = na < 0 ? 0 : k;
+    }
+  }
+  int id[JPT], prev[JPT];
+#pragma unroll
+  for (int q = 0; q < JPT; ++q) {
+    const int j = min(tid + SD_NT * q, k - 1);
+    id[q] = A[j];
+    prev[q] = A[j > 0 ? j - 1 : 0];
+  }
+  int qv[CPT];
+#pragma unroll
+  for (int i = 0; i < CPT; ++i) qv[i] = Q[min(tid + SD_NT * i, C - 1)];
+  sd_clear(s);
+  for (int i = tid; i < KPT * SD_NT / 32; i += SD_NT) s.amask[i] = 0u;
+  lds_barrier();
+  p.store(s, F, C);
+#pragma unroll
+  for (int q = 0; q < JPT; ++q) {
+    const int j = tid + SD_NT * q;
+    if (j < na) {
+      const bool ok = id[q] >= 0 && id[q] < F && (j == 0 || id[q] > prev[q]);
+      if (ok) {
+        ids_s[j] = (uint16_t)id[q];
+        atomicOr(&s.amask[id[q] >> 5], 1u << (id[q] & 31));
+      } else {
+        ids_s[j] = 0;
+        s.bad = 1u;
+      }
+    }
+  }
+  lds_barrier();
+  if (!delta_fast<KPT, CPT, JPT, V4>(l, token, ids_s, na, qv, P, Q, U, out, F, C, k, s, work))
+    delta_checked(l, token, A, na, bad_count, P, Q, U, out, F, C, k, ws, sh.g);
+  else if (bad_count && tid == 0)
+    raise_error(ws, NP_DEVERR_STATE);
+}
+
+// np_delta for any size: one workgroup per layer, the state read from global
+// memory.
 template <int NT, int WPT, int JPT>
 __global__ __launch_bounds__(NT) void delta_kernel(int32_t token,
                                                    const int32_t* __restrict__ active_ids,
@@ -641,8 +1031,6 @@ __global__ __launch_bounds__(NT) void delta_kernel(int32_t token,
   __shared__ uint32_t res[4];
   const int l = blockIdx.x;
   if (token == NP_TOKEN_AUTO) token = *(const int32_t*)((const char*)ws + WS_TOKEN);
-  int32_t* P = slot_of + (size_t)l * F;
-  int32_t* Q = neuron_of + (size_t)l * C;
   // active neurons of this layer: k, or a device count in [0, k]
   int na = k;
   bool bad_count = false;
@@ -653,98 +1041,98 @@ __global__ __launch_bounds__(NT) void delta_kernel(int32_t token,
       na = na < 0 ? 0 : k;
     }
   }
-  const uint32_t none[WPT][32] = {};
-  delta_layer<NT, WPT, JPT, false, false, false>(l, token, active_ids + (size_t)l * k, na,
-                                                 bad_count, P, Q, P, Q, last_used + (size_t)l * F,
-                                                 none, out, F, C, k, spt, ws, amask, smask, rmask,
-                                                 hist, pool, scan, res);
+  delta_layer<NT, WPT, JPT>(l, token, active_ids + (size_t)l * k, na, bad_count,
+                            slot_of + (size_t)l * F, neuron_of + (size_t)l * C,
+                            last_used + (size_t)l * F, out, F, C, k, spt, ws, amask, smask, rmask,
+                            hist, pool, scan, res);
 }
 
 // np_select followed by np_delta in one workgroup per layer.  At entry every
-// thread issues all of its loads at once: the scores of its id word (the
-// selection keys), the last_used values of the same word (the victim keys)
-// and a share of the layer's slot_of and neuron_of, which go to LDS; the delta then finds every slot and back-reference there instead
-// of in global memory, scans the slots and neurons wave by wave, and needs no
-// second launch.  For F <= SD_MAX_F, C <= SD_MAX_C and
-// k <= SD_MAX_K (one id word per thread at 512 threads); the slot pool of the
-// delta shares the selection's histogram.
-
-template <int JPT, bool V4>
+// thread issues its loads at once: a share of slot_of, the scores of its ids
+// (the selection keys) and a share of neuron_of.
+template <int KPT, int CPT, int JPT, bool V4>
 __global__ __launch_bounds__(SD_NT) void select_delta_kernel(
     const float* __restrict__ scores, uint32_t* __restrict__ mask,
     int32_t* __restrict__ active_ids, int32_t token, int32_t* __restrict__ slot_of,
     int32_t* __restrict__ neuron_of, int32_t* __restrict__ last_used, np_delta_out out, int F,
     int C, int k, void* ws) {
-  constexpr int NT = SD_NT;
-  __shared__ __attribute__((aligned(16))) int32_t Ps[SD_MAX_F];  // slot_of of the layer at entry
-  __shared__ int32_t Qs[SD_MAX_C];  // neuron_of of the layer at entry
-  __shared__ int32_t ids_s[SD_MAX_K];
-  __shared__ uint32_t amask[SD_MAX_F / 32], rmask[SD_MAX_F / 32], smask[SD_MAX_C / 32];
-  __shared__ uint32_t hist[4096];  // both selections; then the delta's slot pool
-  __shared__ uint32_t scan[3 * (NT / WAVE) + 1];
-  __shared__ uint32_t res[4];
+  __shared__ __attribute__((aligned(16))) SdShared<KPT> sh;
+  __shared__ uint16_t ids_s[SD_MAX_K];
+  __shared__ uint32_t work[4096 + 3 * SD_NW + 1 + 4];
+  SdLds<KPT>& s = sh.f;
   const int l = blockIdx.x, tid = threadIdx.x;
   if (token == NP_TOKEN_AUTO) token = *(const int32_t*)((const char*)ws + WS_TOKEN);
   const int words = (F + 31) / 32;
   int32_t* P = slot_of + (size_t)l * F;
   int32_t* Q = neuron_of + (size_t)l * C;
   int32_t* U = last_used + (size_t)l * F;
-  // all loads first: slot_of (int4 when its rows are 16-byte aligned), the
-  // selection keys, neuron_of and the victim keys' last_used values.  Loads
-  // complete in order: slot_of goes to LDS as soon as it is in, the
-  // selection waits only for the keys, and neuron_of goes to LDS after it.
-  // (A clamped index loads and stores the last entry again, with the same
-  // value: the loops have no branch, so they unroll and stay in registers.)
-  constexpr int PV = V4 ? SD_PF / 4 : SD_PF;
-  int4 pv4[V4 ? PV : 1];
-  int pv1[V4 ? 1 : PV];
-  if constexpr (V4) {
-    const int4* P4 = reinterpret_cast<const int4*>(P);
+  const float* sc = scores + (size_t)l * F;
+  SlotLoads<KPT, V4> p;
+  p.load(P, F);
+  sd_clear(s);
+  lds_barrier();
+  // (wide unaligned layers: slot_of first, both would not fit the registers)
+  constexpr bool P_FIRST = !V4 && KPT == 32;
+  if constexpr (P_FIRST) p.store(s, F, C);
+  uint32_t key[1][KPT];
+  bool nan = false;
+  if (KPT * tid < F) {
+    float v[KPT];
+    if constexpr (V4) {
+      const int last = F / 4 - 1;
 #pragma unroll
-    for (int i = 0; i < PV; ++i) pv4[i] = P4[min(tid + NT * i, F / 4 - 1)];
+      for (int i = 0; i < KPT / 4; ++i) {
+        const float4 q = reinterpret_cast<const float4*>(sc)[min(KPT / 4 * tid + i, last)];
+        v[4 * i] = q.x;
+        v[4 * i + 1] = q.y;
+        v[4 * i + 2] = q.z;
+        v[4 * i + 3] = q.w;
+      }
+    } else {
+#pragma unroll
+      for (int b = 0; b < KPT; ++b) v[b] = sc[min(KPT * tid + b, F - 1)];
+    }
+#pragma unroll
+    for (int b = 0; b < KPT; ++b) {
+      const uint32_t kv = score_key(v[b], &nan);
+      key[0][b] = KPT * tid + b < F ? kv : 0u;
+    }
   } else {
 #pragma unroll
-    for (int i = 0; i < PV; ++i) pv1[i] = P[min(tid + NT * i, F - 1)];
+    for (int b = 0; b < KPT; ++b) key[0][b] = 0u;
   }
-  uint32_t key[1][32];
-  bool nan = false;
-  load_score_keys<1, V4>(scores + (size_t)l * F, F, tid, key, &nan);
-  int qv[SD_QF];
+  int qv[CPT];
 #pragma unroll
-  for (int i = 0; i < SD_QF; ++i) qv[i] = Q[min(tid + NT * i, C - 1)];
-  uint32_t ukey[1][32] = {};  // with unaligned rows the delta reads them itself
-  if constexpr (V4) {
-    const int4* u4 = reinterpret_cast<const int4*>(U);
-    const int last = F / 4 - 1;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int4 q = u4[min(8 * tid + i, last)];
-      ukey[0][4 * i] = (uint32_t)q.x;
-      ukey[0][4 * i + 1] = (uint32_t)q.y;
-      ukey[0][4 * i + 2] = (uint32_t)q.z;
-      ukey[0][4 * i + 3] = (uint32_t)q.w;
+  for (int i = 0; i < CPT; ++i) qv[i] = Q[min(tid + SD_NT * i, C - 1)];
+  if constexpr (!P_FIRST) p.store(s, F, C);
+  if (nan) raise_error(ws, NP_DEVERR_NAN_SCORE);
+  uint32_t* hint = l < WS_SEL_HINT_LAYERS ? (uint32_t*)((char*)ws + WS_SEL_HINT) + 2 * l : nullptr;
+  uint32_t sel = select_hinted<KPT>(key, (uint32_t)k, s, work, hint);
+  {  // the mask, and the ids in ascending order
+    const uint32_t ww = whole_word<KPT>(sel);
+    const int word = KPT == 32 ? tid : tid >> 1;
+    if (KPT == 32 || (tid & 1) == 0) {
+      s.amask[word] = ww;
+      if (word < words) mask[(size_t)l * words + word] = ww;
+    }
+    uint32_t tot;
+    uint32_t pos = block_excl_scan_once<SD_NT>(__builtin_popcount(sel), s.scan[4], &tot);
+    while (sel) {
+      const int n = KPT * tid + __builtin_ctz(sel);
+      sel &= sel - 1;
+      if (pos < (uint32_t)k) {
+        active_ids[(size_t)l * k + pos] = n;
+        ids_s[pos] = (uint16_t)n;
+      }
+      ++pos;
     }
   }
-  if constexpr (V4) {
-#pragma unroll
-    for (int i = 0; i < PV; ++i)
-      reinterpret_cast<int4*>(Ps)[min(tid + NT * i, F / 4 - 1)] = pv4[i];
-  } else {
-#pragma unroll
-    for (int i = 0; i < PV; ++i) Ps[min(tid + NT * i, F - 1)] = pv1[i];
+  lds_barrier();  // ids_s, s.slot and the masks complete
+  if (!delta_fast<KPT, CPT, JPT, V4>(l, token, ids_s, k, qv, P, Q, U, out, F, C, k, s, work)) {
+    __syncthreads();
+    __threadfence_block();  // the ids are read back from memory
+    delta_checked(l, token, active_ids + (size_t)l * k, k, false, P, Q, U, out, F, C, k, ws, sh.g);
   }
-  if (nan) raise_error(ws, NP_DEVERR_NAN_SCORE);
-  uint32_t sel[1];
-  uint32_t* hint = l < WS_SEL_HINT_LAYERS ? (uint32_t*)((char*)ws + WS_SEL_HINT) + 2 * l : nullptr;
-  select_largest_hinted<NT>(key, (uint32_t)k, sel, hist, scan, res, hint);
-#pragma unroll
-  for (int i = 0; i < SD_QF; ++i) Qs[min(tid + NT * i, C - 1)] = qv[i];
-  write_selection<NT, 1>(sel, tid, words, k, mask + (size_t)l * words,
-                         active_ids + (size_t)l * k, ids_s, scan);
-  __syncthreads();  // ids_s, Ps and Qs complete
-  delta_layer<NT, 1, JPT, true, V4, V4>(l, token, ids_s, k, false, Ps, Qs, P, Q, U, ukey, out, F,
-                                        C, k, 1, ws, amask, smask, rmask, hist, (int32_t*)hist,
-                                        scan, res);
 }
 
 // Centroid choice and the intersected active set (Sec. 3.3-3.4), one
@@ -907,45 +1295,83 @@ static hipError_t delta_w(const np_shape& s, int32_t token, const int32_t* activ
   return hipGetLastError();
 }
 
-hipError_t launch_delta(const np_shape& s, int32_t token, const int32_t* active_ids,
-                        const np_state& st, const np_delta_out& out, void* ws,
-                        hipStream_t stream, const int32_t* counts) {
-  // 512 threads while every thread owns one id word and at most 4 actives
-  const int words = (s.d_ffn + 31) / 32;
-  hipError_t e;
-  if (words <= 512 && s.k <= 2048) e = delta_w<512, 1>(s, token, active_ids, st, out, ws, stream, counts);
-  else if (words <= 1024) e = delta_w<1024, 1>(s, token, active_ids, st, out, ws, stream, counts);
-  else e = delta_w<1024, 2>(s, token, active_ids, st, out, ws, stream, counts);
+// Whether the layer fits the kernels that keep its slot map in LDS.
+static bool fits_lds(const np_shape& s) {
+  return s.d_ffn <= SD_MAX_F && s.capacity <= SD_MAX_C && s.k <= SD_MAX_K;
+}
+
+// Calls f with the sizes of the LDS kernels for this shape: ids, slots and
+// active rows per thread.  Half as many ids per thread keep all 16 waves busy
+// where F allows it.
+template <class Fn>
+static void with_sd_sizes(const np_shape& s, Fn f) {
+  const int jpt = (s.k + SD_NT - 1) / SD_NT;
+  auto j = [&](auto kpt, auto cpt) {
+    if (jpt <= 2) f(kpt, cpt, std::integral_constant<int, 2>());
+    else if (jpt <= 4) f(kpt, cpt, std::integral_constant<int, 4>());
+    else f(kpt, cpt, std::integral_constant<int, 8>());
+  };
+  if (s.d_ffn <= 16 * SD_NT) {
+    if (s.capacity <= 8 * SD_NT) j(std::integral_constant<int, 16>(), std::integral_constant<int, 8>());
+    else j(std::integral_constant<int, 16>(), std::integral_constant<int, 16>());
+  } else {
+    j(std::integral_constant<int, 32>(), std::integral_constant<int, 16>());
+  }
+}
+
+static hipError_t advance_token(int32_t token, void* ws, hipStream_t stream) {
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess || token != NP_TOKEN_AUTO) return e;
   hipLaunchKernelGGL(token_advance_kernel, dim3(1), dim3(64), 0, stream, ws);
   return hipGetLastError();
 }
 
-// np_select then np_delta: the fused kernel where the layer fits it (unless
+hipError_t launch_delta(const np_shape& s, int32_t token, const int32_t* active_ids,
+                        const np_state& st, const np_delta_out& out, void* ws,
+                        hipStream_t stream, const int32_t* counts) {
+  if (fits_lds(s)) {
+    with_sd_sizes(s, [&](auto kpt, auto cpt, auto jpt) {
+      constexpr int K = decltype(kpt)::value, C = decltype(cpt)::value, J = decltype(jpt)::value;
+      if (s.d_ffn % 4 == 0)
+        hipLaunchKernelGGL((delta_lds_kernel<K, C, J, true>), dim3(s.layers), dim3(SD_NT), 0,
+                           stream, token, active_ids, st.slot_of, st.neuron_of, st.last_used, out,
+                           s.d_ffn, s.capacity, s.k, ws, counts);
+      else
+        hipLaunchKernelGGL((delta_lds_kernel<K, C, J, false>), dim3(s.layers), dim3(SD_NT), 0,
+                           stream, token, active_ids, st.slot_of, st.neuron_of, st.last_used, out,
+                           s.d_ffn, s.capacity, s.k, ws, counts);
+    });
+    return advance_token(token, ws, stream);
+  }
+  const hipError_t e =
+      s.d_ffn <= 32 * 1024 ? delta_w<1024, 1>(s, token, active_ids, st, out, ws, stream, counts)
+                           : delta_w<1024, 2>(s, token, active_ids, st, out, ws, stream, counts);
+  return e != hipSuccess ? e : advance_token(token, ws, stream);
+}
+
+// np_select then np_delta: one kernel where the layer fits it (unless
 // NP_SELECT_DELTA_FUSED=0), else the two kernels.
 hipError_t launch_select_delta(const np_shape& s, int32_t token, const float* scores,
                                uint32_t* mask, int32_t* active_ids, const np_state& st,
                                const np_delta_out& out, void* ws, hipStream_t stream) {
   const char* env = getenv("NP_SELECT_DELTA_FUSED");
-  const bool fused = !(env && env[0] == '0') && s.d_ffn <= SD_MAX_F &&
-                     s.capacity <= SD_MAX_C && s.k <= SD_MAX_K;
-  if (!fused) {
+  if ((env && env[0] == '0') || !fits_lds(s)) {
     hipError_t e = launch_select(s, scores, mask, active_ids, ws, stream);
     if (e != hipSuccess) return e;
     return launch_delta(s, token, active_ids, st, out, ws, stream, nullptr);
   }
-  const bool v4 = s.d_ffn % 4 == 0;
-  const int jpt = (s.k + SD_NT - 1) / SD_NT;
-#define NP_SD_CASE(J)                                                                            do {                                                                                             if (v4)                                                                                          hipLaunchKernelGGL((select_delta_kernel<J, true>), dim3(s.layers), dim3(SD_NT), 0,                                stream, scores, mask, active_ids, token, st.slot_of, st.neuron_of,                             st.last_used, out, s.d_ffn, s.capacity, s.k, ws);                         else                                                                                             hipLaunchKernelGGL((select_delta_kernel<J, false>), dim3(s.layers), dim3(SD_NT), 0,                               stream, scores, mask, active_ids, token, st.slot_of, st.neuron_of,                             st.last_used, out, s.d_ffn, s.capacity, s.k, ws);                       } while (0)
-  if (jpt <= 1) NP_SD_CASE(1);
-  else if (jpt <= 2) NP_SD_CASE(2);
-  else if (jpt <= 4) NP_SD_CASE(4);
-  else NP_SD_CASE(8);
-#undef NP_SD_CASE
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || token != NP_TOKEN_AUTO) return e;
-  hipLaunchKernelGGL(token_advance_kernel, dim3(1), dim3(64), 0, stream, ws);
-  return hipGetLastError();
+  with_sd_sizes(s, [&](auto kpt, auto cpt, auto jpt) {
+    constexpr int K = decltype(kpt)::value, C = decltype(cpt)::value, J = decltype(jpt)::value;
+    if (s.d_ffn % 4 == 0)
+      hipLaunchKernelGGL((select_delta_kernel<K, C, J, true>), dim3(s.layers), dim3(SD_NT), 0,
+                         stream, scores, mask, active_ids, token, st.slot_of, st.neuron_of,
+                         st.last_used, out, s.d_ffn, s.capacity, s.k, ws);
+    else
+      hipLaunchKernelGGL((select_delta_kernel<K, C, J, false>), dim3(s.layers), dim3(SD_NT), 0,
+                         stream, scores, mask, active_ids, token, st.slot_of, st.neuron_of,
+                         st.last_used, out, s.d_ffn, s.capacity, s.k, ws);
+  });
+  return advance_token(token, ws, stream);
 }
 
 }  // namespace np

@@ -1,0 +1,153 @@
+"""The kernels that keep a layer's slot map in LDS (np_select_delta, np_delta
+and np_delta_n up to F 32768, C 16384, k 8192) at the edges of their sizes and
+of their shortcuts, against the oracle, bit for bit: ids per thread (F 16384 |
+16385), slots per thread (C 8192 | 8193), actives per thread (k 2048, 4096 |
++ 1), F a multiple of 4 or not, the largest layer and the first ones past it,
+tokens so far apart that the victims' ages leave the histogram, scores tied
+past what one bin resolves, counts from 0 to k, and ids that are no active
+set (reported; nothing out of range is written)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from paper_2608_22643_amd import binding as B
+from paper_2608_22643_amd import workload as W
+from gpu_util import Bufs, compare_delta, from_dev, say
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # L, F, k, C
+    (2, 16384, 2048, 8192), (2, 16385, 2049, 8193), (1, 16383, 4097, 8193),
+    (1, 20002, 1999, 16384), (1, 32768, 8192, 16384), (1, 32767, 4096, 9000),
+    (1, 32768, 3000, 16385), (1, 32769, 3000, 9000), (3, 65, 7, 9), (2, 31, 31, 31),
+]
+
+
+def cfg_of(L, F, k, C):
+    return W.Config("lds", L, 64, F, 8, k / F, C / F, "f32", "f32", 4, rho_given=0.9, k_override=k,
+                    c_override=C)
+
+
+def check_state(bufs, st):
+    P, Q, U = bufs.host_state()
+    assert np.array_equal(P, st.slot_of) and np.array_equal(Q, st.neuron_of)
+    assert np.array_equal(U, st.last_used)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "L%d_F%d_k%d_C%d" % s)
+def test_delta_lds_sizes(shape):
+    L, F, k, C = shape
+    cfg = cfg_of(*shape)
+    say(f"[delta lds] {shape}")
+    rng = np.random.default_rng(F + k)
+    bufs, two = Bufs(cfg), Bufs(cfg)
+    bufs.reset()
+    two.reset()
+    st = orc.State(L, F, C)
+    s = rng.standard_normal((L, F))
+    # tokens 3000 apart: some victims are more than a histogram older than others
+    for i, token in enumerate((0, 1, 2, 3, 3003, 3004, 6100, 6101, 6102)):
+        s = 0.9 * s + np.sqrt(1 - 0.81) * rng.standard_normal((L, F))
+        v = s.astype(np.float32)
+        if i in (2, 5):
+            v = np.round(v * 4) / np.float32(4)  # more equal keys than a bin resolves
+        if i == 6:
+            v[:] = 1.5  # one value: the ids decide
+        dev = torch.from_numpy(v.reshape(-1)).cuda()
+        B.np_select_delta(bufs.shape, token, dev, bufs.mask, bufs.ids, bufs.state, bufs.out, bufs.ws)
+        B.np_select(two.shape, dev, two.mask, two.ids, two.ws)
+        B.np_delta(two.shape, token, two.ids, two.state, two.out, two.ws)
+        torch.cuda.synchronize()
+        mask, ids = orc.select(v, k)
+        assert np.array_equal(from_dev(bufs.ids, np.int32, (L, k)), ids), i
+        assert torch.equal(bufs.mask, two.mask)
+        assert np.array_equal(from_dev(bufs.mask, np.uint32, mask.shape), mask), i
+        ref = orc.delta(token, ids, st, C)
+        for b in (bufs, two):
+            compare_delta(b.host_lists(), ref, L)
+            check_state(b, st)
+            assert B.np_device_error(b.ws) == 0
+
+
+@pytest.mark.parametrize("shape", [(3, 11008, 1651, 5504), (2, 14337, 5500, 7168)],
+                         ids=["aligned", "odd"])
+def test_delta_lds_counts(shape):
+    """np_delta_n with counts 0 .. k against the oracle."""
+    L, F, k, C = shape
+    cfg = cfg_of(*shape)
+    say(f"[delta lds counts] {shape}")
+    rng = np.random.default_rng(5)
+    bufs = Bufs(cfg)
+    bufs.reset()
+    st = orc.State(L, F, C)
+    for token in range(6):
+        counts = rng.integers(0, k + 1, size=L).astype(np.int32)
+        counts[token % L] = (0, k, 1)[token % 3]
+        ids = np.zeros((L, k), np.int32)
+        for l in range(L):
+            ids[l, :counts[l]] = np.sort(rng.choice(F, counts[l], replace=False))
+        pad = np.zeros(max(L, 4), np.int32)
+        pad[:L] = counts
+        B.np_delta_n(bufs.shape, token, torch.from_numpy(ids).cuda(), torch.from_numpy(pad).cuda(),
+                     bufs.state, bufs.out, bufs.ws)
+        torch.cuda.synchronize()
+        ref = orc.delta_n(token, ids, counts, st, C)
+        got = bufs.host_lists()
+        for l in range(L):
+            assert np.array_equal(got["counts"][l], ref["counts"][l]), (token, l)
+            n = counts[l]
+            assert np.array_equal(got["active_slots"][l][:n], ref["active_slots"][l][:n]), (token, l)
+        check_state(bufs, st)
+        assert B.np_device_error(bufs.ws) == 0
+
+
+@pytest.mark.parametrize("bad", ["range", "descending", "slot_range", "unpaired"])
+def test_delta_lds_bad_inputs(bad):
+    """Ids that are no ascending neuron ids, slots outside the layer and
+    unpaired entries set NP_DEVERR_STATE; every entry stays in range."""
+    L, F, k, C = 2, 11008, 300, 900
+    cfg = cfg_of(L, F, k, C)
+    say(f"[delta lds bad] {bad}")
+    rng = np.random.default_rng(8)
+    bufs = Bufs(cfg)
+    bufs.reset()
+
+    def step(token, ids):
+        B.np_delta(bufs.shape, token, torch.from_numpy(ids).cuda(), bufs.state, bufs.out, bufs.ws)
+        torch.cuda.synchronize()
+
+    def draw():
+        return np.stack([np.sort(rng.choice(F, k, replace=False)) for _ in range(L)]).astype(np.int32)
+
+    for token in range(4):
+        step(token, draw())
+    assert B.np_device_error(bufs.ws) == 0
+    ids = draw()
+    if bad == "range":
+        ids[0, -1] = F + 5
+        ids[1, 0] = -3
+    elif bad == "descending":
+        ids[0, 10], ids[0, 11] = ids[0, 11], ids[0, 10]
+    elif bad == "slot_range":
+        bufs.slot_of.view(L, F)[1, 77] = C + 4
+        ids[1] = np.sort(np.r_[77, 100 + rng.choice(F - 100, k - 1, replace=False)])
+    else:
+        Q = bufs.neuron_of.view(L, C)
+        Q[0, 3] = (int(Q[0, 3]) + 1) % F
+    if bad == "descending":  # the same set: a defined result, whatever the order
+        st_ids = np.sort(ids, axis=1)
+        step(4, ids)
+        hit = bufs.host_lists()["active_slots"]
+        P, Q, _ = bufs.host_state()
+        for l in range(L):
+            assert np.array_equal(P[l][ids[l]], hit[l])
+            assert np.all(P[l][st_ids[l]] >= 0)
+        assert B.np_device_error(bufs.ws) == 0
+        return
+    step(4, ids)
+    assert B.np_device_error(bufs.ws) & B.NP_DEVERR_STATE
+    lists = bufs.host_lists()
+    assert np.all(lists["active_slots"] < C) and np.all(lists["active_slots"] >= -1)
+    P, Q, _ = bufs.host_state()
+    assert np.all(Q < F) and np.all(Q >= -1)
