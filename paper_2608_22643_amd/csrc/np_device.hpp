@@ -392,6 +392,23 @@ __device__ inline uint32_t block_excl_scan_once(uint32_t v, uint32_t* lds, uint3
   return before + incl - v;
 }
 
+// Exclusive prefix over the waves of a value that is the same in every lane
+// of a wave (at most 16 waves); barrier and lds as above.
+__device__ inline uint32_t wave_prefix_once(uint32_t v, uint32_t* lds, int nw, uint32_t* total) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
+  if (lane == 0) lds[w] = v;
+  lds_barrier();
+  const uint32_t t = row_incl_scan(lane < nw ? lds[lane] : 0u);
+  *total = (uint32_t)__builtin_amdgcn_readlane((int)t, nw - 1);
+  return w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)t, w > 0 ? w - 1 : 0) : 0u;
+}
+
+// Set bits of m below this lane.
+__device__ inline uint32_t lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 // The same with lds free for reuse on return (a second barrier).
 template <int NT>
 __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t* lds, uint32_t* total) {
@@ -438,12 +455,15 @@ __device__ inline void raise_error(void* ws, int bits) {
 // of the ties.  hist: 4096 uint32 of LDS; scan: 3*NT/64 + 1 uint32; res: 4
 // uint32.
 // ---------------------------------------------------------------------------
+// block_find_kth: the kk-th largest key alone, and in *take how many of the
+// keys equal to it belong to the kk largest (or more than there are: all);
+// it does not ask which thread owns which id.
 constexpr uint32_t SEL_SMALL_CAND = 1024;  // at most this many keys left: 8-bit passes
 
 template <int NT, int WPT, int KB>
-__device__ inline void block_select_largest(const uint32_t (&key)[WPT][KB], uint32_t kk,
-                                            uint32_t (&sel)[WPT], uint32_t* hist,
-                                            uint32_t* scan, uint32_t* res) {
+__device__ inline uint32_t block_find_kth(const uint32_t (&key)[WPT][KB], uint32_t kk,
+                                          uint32_t* take, uint32_t* hist, uint32_t* scan,
+                                          uint32_t* res) {
   constexpr int NW = NT / WAVE;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
   // count, max and min of the nonzero keys
@@ -595,6 +615,16 @@ __device__ inline void block_select_largest(const uint32_t (&key)[WPT][KB], uint
       }
     }
   }
+  *take = rem;
+  return prefix;
+}
+
+template <int NT, int WPT, int KB>
+__device__ inline void block_select_largest(const uint32_t (&key)[WPT][KB], uint32_t kk,
+                                            uint32_t (&sel)[WPT], uint32_t* hist,
+                                            uint32_t* scan, uint32_t* res) {
+  uint32_t rem;
+  const uint32_t prefix = block_find_kth<NT, WPT, KB>(key, kk, &rem, hist, scan, res);
   // prefix is the kk-th largest key; take all larger keys and the first `rem`
   // equal keys in id order.
   uint32_t eqm[WPT], neq = 0;

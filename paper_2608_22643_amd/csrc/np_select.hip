@@ -17,13 +17,11 @@ namespace np {
 // -0.0 maps to the key of +0.0.  NaN maps to 0 (below every other key) and
 // is reported through the error word.
 __device__ inline uint32_t score_key(float f, bool* nan) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x007FFFFFu)) {
-    *nan = true;
-    return 0u;
-  }
-  if (u == 0x80000000u) u = 0u;
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  const bool bad = f != f;
+  *nan |= bad;
+  const uint32_t u = __float_as_uint(f + 0.f);  // -0.0 + 0.0 is +0.0, all else itself
+  const uint32_t key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+  return bad ? 0u : key;
 }
 
 // Keys of thread tid's id words [tid*WPT, tid*WPT+WPT) of one layer's
@@ -356,67 +354,103 @@ __device__ inline void delta_layer(int l, int32_t token, const int32_t* A, int n
 // threads of 32 ids and about 45 barriers; 70B: 22.3 + 21.2 us in two kernels
 // that read the state from memory.  The figures now are at the launch rule.
 // ---------------------------------------------------------------------------
-constexpr int SD_NT = 1024;
-constexpr int SD_NW = SD_NT / WAVE;
-constexpr int SD_MAX_F = 32 * SD_NT;  // 32768
-constexpr int SD_MAX_C = 16 * SD_NT;  // 16384
+constexpr int SD_MAX_F = 32768;
+constexpr int SD_MAX_C = 16384;
 constexpr int SD_MAX_K = 8192;
-constexpr int SD_BINS = 2048;         // fine bins of a histogram
-constexpr int SD_COARSE = 64;         // coarse bins: SD_BINS / 64 fine ones each
-constexpr int SD_CAND = 64;           // keys of a bin resolved by one wave
+constexpr int SD_BINS = 256;   // bins of the selection's window: four a lane
+constexpr int SD_AGES = WAVE;  // bins of the victims' ages: one a lane
+constexpr int SD_CAND = 64;    // keys of a bin resolved by one wave
 
-// LDS of the fast path (F ids of KPT per thread)
-template <int KPT>
+// Sizes of one build: NT threads, KPT rows of 64 ids per wave, CPT slots and
+// JPT active rows per thread.
+template <int NT_, int KPT_, int CPT_, int JPT_>
+struct Sd {
+  static constexpr int NT = NT_, KPT = KPT_, CPT = CPT_, JPT = JPT_;
+  static constexpr int NW = NT / WAVE, F = KPT * NT, C = CPT * NT, WORDS = F / 32;
+  static_assert(KPT <= 32 && WORDS <= NT, "a row's words fit a wave's lanes, a thread owns a word");
+};
+
+// LDS of the fast path.  Key work: wave w owns KPT rows of 64 consecutive
+// ids, lane i id 64 (w KPT + r) + i of row r, so loads are whole lines and a
+// ballot is two mask words.  Ordered work: thread t owns mask word t.
+template <class S>
 struct SdLds {
-  int16_t slot[KPT * SD_NT];            // slot_of at entry
-  uint16_t pool[SD_MAX_K];              // slots for the incoming rows, ascending
-  uint32_t amask[KPT * SD_NT / 32], rmask[KPT * SD_NT / 32];  // active, resident
-  uint32_t smask[SD_MAX_F / 32];        // free slots, then also the victims'
-  uint32_t hist[SD_BINS], coarse[SD_COARSE];
-  uint32_t vhist[SD_BINS], vcoarse[SD_COARSE];  // the victims'
-  uint32_t cand[SD_CAND], scan[8][SD_NW];
+  int16_t slot[S::F];              // slot_of at entry
+  uint16_t ids[SD_MAX_K], pool[SD_MAX_K];  // active ids; slots for the incoming rows
+  alignas(16) uint32_t smask[SD_MAX_C / 32];  // free slots, then also the victims'
+  uint32_t amask[S::WORDS], rmask[S::WORDS];  // active, resident
+  uint32_t gmask[S::WORDS], emask[S::WORDS];  // keys above, equal to the k-th
+  alignas(16) uint32_t hist[SD_BINS];
+  uint32_t vhist[SD_AGES];
+  uint32_t cand[SD_CAND], scan[8][S::NW];
   uint32_t above, ncand, vmax, used, valid, nfree, bad;
 };
 // LDS of delta_checked, when the slot map is inconsistent
 struct SdChecked {
   uint32_t amask[SD_MAX_F / 32], smask[SD_MAX_F / 32], rmask[SD_MAX_F / 32], hist[256];
   int32_t pool[SD_MAX_K], held[SD_MAX_K];
-  uint32_t scan[SD_NW];
+  uint32_t scan[16];
 };
-template <int KPT>
+template <class S>
 union SdShared {
-  SdLds<KPT> f;
+  SdLds<S> f;
   SdChecked g;
 };
 
-// The bin of a histogram (fine, coarse: filled alike) that holds the rem-th
-// key counted from bin 0 up, and the keys before it; every wave by itself.
-// Returns false when the histogram holds fewer than rem.
-__device__ inline bool find_bin(const uint32_t* fine, const uint32_t* coarse, uint32_t rem,
-                                uint32_t* bin, uint32_t* before, uint32_t* count) {
-  constexpr int PER = SD_BINS / SD_COARSE;
-  const int lane = threadIdx.x & (WAVE - 1);
-  const uint32_t c = wave_incl_scan(coarse[lane]);
-  const uint64_t hit = __ballot(c >= rem);
-  if (!hit) return false;
-  const int cb = __builtin_ctzll(hit);
-  const uint32_t cbefore = cb > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)c, cb > 0 ? cb - 1 : 0) : 0u;
-  const uint32_t v = lane < PER ? fine[cb * PER + lane] : 0u;
-  const uint32_t f = wave_incl_scan(v) + cbefore;
-  const int fb = __builtin_ctzll(__ballot(f >= rem));
-  *count = (uint32_t)__builtin_amdgcn_readlane((int)v, fb);
-  *before = (uint32_t)__builtin_amdgcn_readlane((int)f, fb) - *count;
-  *bin = (uint32_t)(cb * PER + fb);
-  return true;
+__device__ inline int wave_id() {
+  return __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
+}
+template <int KPT>
+__device__ inline int sd_id(int r) {
+  return WAVE * (wave_id() * KPT + r) + (int)(threadIdx.x & (WAVE - 1));
+}
+// 32-bit loads of a layer's row of n entries: one address register for all
+// rows, entries past the end read as 0 without a memory access.
+struct RowLoads {
+  __amdgpu_buffer_rsrc_t rs;
+  uint32_t off;
+  __device__ inline RowLoads(const void* p, int n, int first)
+      : rs(make_rsrc(p, (uint32_t)n * 4u)), off((uint32_t)first * 4u) {}
+  __device__ inline uint32_t at(int r) const {  // entry first + 64 r
+    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(off + 256u * (uint32_t)r), 0, 0);
+  }
+};
+
+// The wave's rows of a predicate to mask words in LDS.
+template <int KPT, class Fn>
+__device__ inline void store_rows(uint32_t* words, Fn pred) {
+  uint64_t b[KPT];
+#pragma unroll
+  for (int r = 0; r < KPT; ++r) b[r] = __ballot(pred(r));
+  if ((threadIdx.x & (WAVE - 1)) == 0) {
+    uint64_t* w = reinterpret_cast<uint64_t*>(words) + KPT * wave_id();
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) w[r] = b[r];
+  }
 }
 
-// bits b of words that two threads share (KPT = 16) or own (32): the word of
-// ids 32 w .. 32 w + 31 in the thread that holds its low bits
-template <int KPT>
-__device__ inline uint32_t whole_word(uint32_t bits) {
-  if constexpr (KPT == 32) return bits;
-  const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)bits, DPP_XOR1, 0xF, 0xF, true);
-  return bits | (other << 16);  // of use in even lanes
+// The bin of a 256-bin histogram that holds the rem-th key counted from bin 0
+// up, the keys before it, its count, and all keys; every wave by itself.
+// Returns false when the histogram holds fewer than rem.
+__device__ inline bool find_bin(const uint32_t* hist, uint32_t rem, uint32_t* bin,
+                                uint32_t* before, uint32_t* count, uint32_t* total) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  const uint4 h = reinterpret_cast<const uint4*>(hist)[lane];
+  const uint32_t sum = h.x + h.y + h.z + h.w;
+  const uint32_t incl = wave_incl_scan(sum);
+  *total = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+  const uint64_t hit = __ballot(incl >= rem);
+  if (!hit) return false;
+  // within the lane: the first of its four bins that reaches rem
+  uint32_t acc = incl - sum, b = 0, c = h.x;
+  if (acc + c < rem) acc += c, b = 1, c = h.y;
+  if (acc + c < rem) acc += c, b = 2, c = h.z;
+  if (acc + c < rem) acc += c, b = 3, c = h.w;
+  const int at = __builtin_ctzll(hit);
+  *bin = 4u * (uint32_t)at + (uint32_t)__builtin_amdgcn_readlane((int)b, at);
+  *before = (uint32_t)__builtin_amdgcn_readlane((int)acc, at);
+  *count = (uint32_t)__builtin_amdgcn_readlane((int)c, at);
+  return true;
 }
 
 // The k largest keys of the layer (ties to the smaller ids), starting from a
@@ -426,17 +460,21 @@ __device__ inline uint32_t whole_word(uint32_t bits) {
 // keys above the window and puts those inside into a histogram; every wave
 // finds the k-th key's bin, and the few keys of that bin decide.  Whatever the
 // hint holds, the result is the same: when the k-th key is outside the window
-// or its bin holds more than SD_CAND keys, the full radix select runs.  The
-// hint is updated: the new k-th key, the window halved when it held many keys,
-// quadrupled when the k-th key fell outside it.
-constexpr uint32_t SEL_HINT_MANY = 960;
+// or its bin holds more than SD_CAND keys, the full radix search runs.  The
+// hint is updated: the new k-th key, the window halved when it held many keys
+// (each costs an LDS atomic), quadrupled when the k-th key fell outside it.
+// At 7B it settles between 120 and 240 keys, half-widths of 0.02 to 0.05 in
+// score, against steps of the k-th key of about 0.004.
+constexpr uint32_t SEL_HINT_MANY = 240;
 constexpr uint32_t SEL_HINT_HALF0 = 1u << 20;  // first window half-width (fp32 keys: 0.125 at 1.0)
 
-template <int KPT>
-__device__ inline uint32_t select_hinted(const uint32_t (&key)[1][KPT], uint32_t kk,
-                                         SdLds<KPT>& s, uint32_t* work, uint32_t* hint) {
+// Leaves the selected ids in s.amask, behind a barrier.
+template <class S>
+__device__ inline void select_hinted(const uint32_t (&key)[1][S::KPT], uint32_t kk, SdLds<S>& s,
+                                     uint32_t* work, uint32_t* hint, uint32_t hkey,
+                                     uint32_t half) {
+  constexpr int KPT = S::KPT;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1);
-  const uint32_t hkey = hint ? hint[0] : 0u, half = hint ? hint[1] : 0u;
   const uint32_t lo = hkey > half ? hkey - half : 1u;
   const uint32_t hi = hkey < 0xFFFFFFFFu - half ? hkey + half : 0xFFFFFFFFu;
   const bool window = hkey != 0u && half != 0u;
@@ -445,32 +483,26 @@ __device__ inline uint32_t select_hinted(const uint32_t (&key)[1][KPT], uint32_t
   if (window) {
     const uint32_t width = hi - lo;  // bins of 2^shift keys, from the top
     const int bits = width ? 32 - __builtin_clz(width) : 0;
-    const int shift = bits > 11 ? bits - 11 : 0;
+    const int shift = bits > 8 ? bits - 8 : 0;
     uint32_t above = 0;
 #pragma unroll
-    for (int b = 0; b < KPT; ++b) {
-      const uint32_t d = hi - key[0][b];  // keys above hi wrap past width
-      above += key[0][b] > hi;
-      if (key[0][b] <= hi && d <= width) {
-        atomicAdd(&s.hist[d >> shift], 1u);
-        atomicAdd(&s.coarse[(d >> shift) / (SD_BINS / SD_COARSE)], 1u);
-      }
+    for (int r = 0; r < KPT; ++r) {
+      const uint32_t d = hi - key[0][r];  // a key above hi wraps to more than hi >= width
+      above += (uint32_t)__popcll(__ballot(d > hi));
+      if (d <= width) atomicAdd(&s.hist[d >> shift], 1u);
     }
-    above = wave_total(above);
     if (lane == 0 && above) atomicAdd(&s.above, above);
     lds_barrier();
     above = s.above;
     uint32_t bin = 0, before = 0, count = 0;
-    use = above < kk && find_bin(s.hist, s.coarse, kk - above, &bin, &before, &count) &&
+    use = above < kk && find_bin(s.hist, kk - above, &bin, &before, &count, &inside) &&
           count <= SD_CAND;
     if (use) {  // the keys of the bin, in any order
       const uint32_t rem = kk - above - before;
+      const uint32_t first = bin << shift, last = min((uint32_t)((1u << shift) - 1u), width - first);
 #pragma unroll
-      for (int b = 0; b < KPT; ++b) {
-        const uint32_t d = hi - key[0][b];
-        if (key[0][b] <= hi && d <= width && (d >> shift) == bin)
-          s.cand[atomicAdd(&s.ncand, 1u)] = key[0][b];
-      }
+      for (int r = 0; r < KPT; ++r)
+        if (hi - first - key[0][r] <= last) s.cand[atomicAdd(&s.ncand, 1u)] = key[0][r];
       lds_barrier();
       const uint32_t mine = (uint32_t)lane < count ? s.cand[lane] : 0u;
       uint32_t gt = 0, eq = 0;  // keys of the bin above this lane's, equal to it
@@ -483,43 +515,29 @@ __device__ inline uint32_t select_hinted(const uint32_t (&key)[1][KPT], uint32_t
       kth = (uint32_t)__builtin_amdgcn_readlane((int)mine, at);
       eq_take = rem - (uint32_t)__builtin_amdgcn_readlane((int)gt, at);
       eq_all = (uint32_t)__builtin_amdgcn_readlane((int)eq, at);
-      inside = wave_total(s.coarse[lane]);
     }
   }
-  uint32_t sel[1];
-  if (use) {
-    uint32_t gt = 0, eq = 0;
-#pragma unroll
-    for (int b = 0; b < KPT; ++b) {
-      gt |= (key[0][b] > kth ? 1u : 0u) << b;
-      eq |= (key[0][b] == kth ? 1u : 0u) << b;
-    }
-    if (eq_take == eq_all) {
-      sel[0] = gt | eq;
-    } else {  // the first eq_take of the equal keys, in id order
-      uint32_t tot;
-      uint32_t n = block_excl_scan_once<SD_NT>(__builtin_popcount(eq), s.scan[0], &tot);
-      while (eq && n < eq_take) {
-        gt |= eq & (0u - eq);
-        eq &= eq - 1;
-        ++n;
-      }
-      sel[0] = gt;
-    }
-  } else {
+  if (!use) {
     __syncthreads();  // every wave is done with the window's histogram
-    block_select_largest<SD_NT, 1>(key, kk, sel, work, work + 4096, work + 4096 + 3 * SD_NW + 1);
-    if (hint) {  // the k-th key: the smallest selected one
-      uint32_t mx = 0;
-#pragma unroll
-      for (int b = 0; b < KPT; ++b)
-        if (((sel[0] >> b) & 1u) && ~key[0][b] > mx) mx = ~key[0][b];
-      mx = wave_max(mx);
-      if (lane == 0) s.scan[0][tid / WAVE] = mx;
-      __syncthreads();
-      for (int i = 0; i < SD_NW; ++i) mx = s.scan[0][i] > mx ? s.scan[0][i] : mx;
-      kth = ~mx;  // 0 when a NaN or padding key was taken
+    kth = block_find_kth<S::NT, 1>(key, kk, &eq_take, work, work + 4096,
+                                   work + 4096 + 3 * S::NW + 1);
+  }
+  if (use && eq_take == eq_all) {  // every equal key is taken (usually the one)
+    store_rows<KPT>(s.amask, [&](int r) { return key[0][r] >= kth; });
+    lds_barrier();
+  } else {  // the first eq_take of them in id order
+    store_rows<KPT>(s.gmask, [&](int r) { return key[0][r] > kth; });
+    store_rows<KPT>(s.emask, [&](int r) { return key[0][r] == kth; });
+    lds_barrier();
+    uint32_t sel = tid < S::WORDS ? s.gmask[tid] : 0u, eq = tid < S::WORDS ? s.emask[tid] : 0u, tot;
+    uint32_t n = block_excl_scan_once<S::NT>(__builtin_popcount(eq), s.scan[0], &tot);
+    while (eq && n < eq_take) {
+      sel |= eq & (0u - eq);
+      eq &= eq - 1;
+      ++n;
     }
+    if (tid < S::WORDS) s.amask[tid] = sel;
+    lds_barrier();
   }
   if (hint && tid == 0) {
     uint32_t h = half ? half : SEL_HINT_HALF0;
@@ -528,116 +546,60 @@ __device__ inline uint32_t select_hinted(const uint32_t (&key)[1][KPT], uint32_t
     } else if (window) {
       h = h < (1u << 29) ? h << 2 : h;
     }
-    hint[0] = kth;
+    hint[0] = kth;  // 0 when NaN keys were taken
     hint[1] = h;
   }
-  return sel[0];
 }
 
-// slot_of of one layer to LDS, with the resident bits and the counts of valid
-// entries; an entry outside {-1} and [0, C) sets bad.  V4: the rows of the
-// layer are 16-byte aligned (F a multiple of 4).
-template <int KPT, bool V4>
-struct SlotLoads {
-  int4 v4[V4 ? KPT / 4 : 1];
-  int v1[V4 ? 1 : KPT];
-  __device__ inline void load(const int32_t* P, int F) {
-    const int tid = threadIdx.x;
-    if constexpr (V4) {
-#pragma unroll
-      for (int i = 0; i < KPT / 4; ++i)
-        v4[i] = reinterpret_cast<const int4*>(P)[min(tid + SD_NT * i, F / 4 - 1)];
-    } else {
-#pragma unroll
-      for (int i = 0; i < KPT; ++i) v1[i] = P[min(tid + SD_NT * i, F - 1)];
-    }
-  }
-  __device__ inline void store(SdLds<KPT>& s, int F, int C) {
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
-    uint32_t valid = 0;
-    bool bad = false;
-    if constexpr (V4) {
-#pragma unroll
-      for (int i = 0; i < KPT / 4; ++i) {
-        const int g = tid + SD_NT * i;
-        const bool in = 4 * g < F;
-        const int e[4] = {v4[i].x, v4[i].y, v4[i].z, v4[i].w};
-        uint32_t m = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          bad |= in && (e[c] < -1 || e[c] >= C);
-          m |= (in && e[c] >= 0 ? 1u : 0u) << c;
-        }
-        valid += __builtin_popcount(m);
-        *(uint2*)&s.slot[4 * g] = make_uint2((uint32_t)(e[0] & 0xFFFF) | ((uint32_t)e[1] << 16),
-                                             (uint32_t)(e[2] & 0xFFFF) | ((uint32_t)e[3] << 16));
-        m <<= 4 * (lane & 7);  // eight lanes hold a word's nibbles
-        m |= (uint32_t)__builtin_amdgcn_mov_dpp((int)m, DPP_XOR1, 0xF, 0xF, true);
-        m |= (uint32_t)__builtin_amdgcn_mov_dpp((int)m, DPP_XOR2, 0xF, 0xF, true);
-        m |= (uint32_t)__builtin_amdgcn_mov_dpp((int)m, DPP_XOR7, 0xF, 0xF, true);
-        if ((lane & 7) == 0) s.rmask[g >> 3] = m;
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < KPT; ++i) {
-        const int n = tid + SD_NT * i;
-        const bool in = n < F;
-        bad |= in && (v1[i] < -1 || v1[i] >= C);
-        const uint64_t m = __ballot(in && v1[i] >= 0);
-        valid += lane == 0 ? (uint32_t)__popcll(m) : 0u;
-        s.slot[n] = (int16_t)v1[i];
-        if (lane == 0) *(uint2*)&s.rmask[n >> 5] = make_uint2((uint32_t)m, (uint32_t)(m >> 32));
-      }
-    }
-    valid = wave_total(valid);
-    if (lane == 0 && valid) atomicAdd(&s.valid, valid);
-    if (bad) s.bad = 1u;
-  }
-};
+// slot_of of one layer to LDS, its resident bits to s.rmask, the valid entries
+// counted; an entry outside {-1} and [0, C) sets bad.
+template <class S>
+__device__ inline void store_slots(const uint32_t (&v)[S::KPT], SdLds<S>& s, int F, int C) {
+  uint32_t valid = 0, odd = 0;
+  store_rows<S::KPT>(s.rmask, [&](int r) {
+    const int n = sd_id<S::KPT>(r);
+    s.slot[n] = (int16_t)v[r];
+    const bool in = n < F;
+    odd |= in ? (uint32_t)(v[r] + 1u > (uint32_t)C) : 0u;
+    const bool held = in && (int)v[r] >= 0;
+    valid += (uint32_t)__popcll(__ballot(held));
+    return held;
+  });
+  if ((threadIdx.x & (WAVE - 1)) == 0 && valid) atomicAdd(&s.valid, valid);
+  if (odd) s.bad = 1u;
+}
 
 // Clears the counters and histograms; a barrier must follow before their use.
-template <int KPT>
-__device__ inline void sd_clear(SdLds<KPT>& s) {
+template <class S>
+__device__ inline void sd_clear(SdLds<S>& s) {
   const int tid = threadIdx.x;
-#pragma unroll
-  for (int i = 0; i < SD_BINS / SD_NT; ++i) s.hist[tid + SD_NT * i] = s.vhist[tid + SD_NT * i] = 0u;
-  if (tid < SD_COARSE) s.coarse[tid] = s.vcoarse[tid] = 0u;
+  if (tid < SD_BINS) s.hist[tid] = 0u;
+  if (tid < SD_AGES) s.vhist[tid] = 0u;
   if (tid == 0) s.above = s.ncand = s.vmax = s.used = s.valid = s.nfree = s.bad = 0u;
 }
 
-// The delta of one layer with a consistent slot map in LDS.  qv: this
-// thread's neuron_of entries (slot tid + 1024 i); ids: the layer's active ids
-// in LDS (16 bits, ascending); s.slot, s.amask, s.rmask, s.valid and s.bad
-// complete behind a barrier.  Returns false, having written nothing, when the
-// slot map turns out inconsistent.
-template <int KPT, int CPT, int JPT, bool V4>
-__device__ inline bool delta_fast(int l, int32_t token, const uint16_t* ids, int na,
-                                  const int (&qv)[CPT], int32_t* P, int32_t* Q, int32_t* U,
-                                  const np_delta_out& out, int F, int C, int k, SdLds<KPT>& s,
+// The delta of one layer with a consistent slot map in LDS.  qv: this thread's
+// neuron_of entries (slot tid + NT i); s.ids: the na active ids, ascending,
+// also written to ids_out when that is not null; s.slot, s.amask, s.rmask,
+// s.valid and s.bad complete behind a barrier.  Returns false, having written
+// nothing, when the slot map turns out inconsistent.
+template <class S>
+__device__ inline bool delta_fast(int l, int32_t token, int na, const int (&qv)[S::CPT],
+                                  int32_t* P, int32_t* Q, int32_t* U, int32_t* ids_out,
+                                  const np_delta_out& out, int F, int C, int k, SdLds<S>& s,
                                   uint32_t* work) {
+  constexpr int KPT = S::KPT, CPT = S::CPT, JPT = S::JPT, NT = S::NT;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1);
   const size_t lo = (size_t)l * k;
-  // the ids' last_used, for the victims (in flight meanwhile)
+  // the ids' last_used, for the victims: in flight from here on, or from
+  // behind step 1 where the registers do not hold both
   uint32_t key[1][KPT];
-  if (KPT * tid < F) {
-    if constexpr (V4) {
-      const int last = F / 4 - 1;
+  const RowLoads used_rows(U, F, sd_id<KPT>(0));
+  auto load_used = [&] {
 #pragma unroll
-      for (int i = 0; i < KPT / 4; ++i) {
-        const int4 q = reinterpret_cast<const int4*>(U)[min(KPT / 4 * tid + i, last)];
-        key[0][4 * i] = (uint32_t)q.x;
-        key[0][4 * i + 1] = (uint32_t)q.y;
-        key[0][4 * i + 2] = (uint32_t)q.z;
-        key[0][4 * i + 3] = (uint32_t)q.w;
-      }
-    } else {
-#pragma unroll
-      for (int b = 0; b < KPT; ++b) key[0][b] = (uint32_t)U[min(KPT * tid + b, F - 1)];
-    }
-  } else {
-#pragma unroll
-    for (int b = 0; b < KPT; ++b) key[0][b] = 0u;
-  }
+    for (int r = 0; r < KPT; ++r) key[0][r] = used_rows.at(r);
+  };
+  if constexpr (KPT < 32) load_used();
   // 1. free slots, and the consistency of the map: a used slot's neuron must
   //    map back to it, and no more neurons may hold slots than slots are used
   {
@@ -649,14 +611,15 @@ __device__ inline bool delta_fast(int l, int32_t token, const uint16_t* ids, int
     bool bad = false;
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
-      const int sl = tid + SD_NT * i;
-      const bool in = sl < C, fr = in && qv[i] == -1, us = in && qv[i] != -1;
-      bad |= us && back[i] != sl;
-      const uint64_t fm = __ballot(fr);
-      nfree += (uint32_t)__popcll(fm);
-      used += (uint32_t)__popcll(__ballot(us));
-      if (lane == 0 && SD_NT * i < C)
-        *(uint2*)&s.smask[sl >> 5] = make_uint2((uint32_t)fm, (uint32_t)(fm >> 32));
+      if (NT * i < C) {
+        const int sl = tid + NT * i;
+        const bool in = sl < C, fr = in && qv[i] == -1, us = in && qv[i] != -1;
+        bad |= us && back[i] != sl;
+        const uint64_t fm = __ballot(fr);
+        nfree += (uint32_t)__popcll(fm);
+        used += (uint32_t)__popcll(__ballot(us));
+        if (lane == 0) *(uint2*)&s.smask[sl >> 5] = make_uint2((uint32_t)fm, (uint32_t)(fm >> 32));
+      }
     }
     if (lane == 0) {
       if (nfree) atomicAdd(&s.nfree, nfree);
@@ -664,18 +627,22 @@ __device__ inline bool delta_fast(int l, int32_t token, const uint16_t* ids, int
     }
     if (bad) s.bad = 1u;
   }
+  if constexpr (KPT == 32) {
+    __builtin_amdgcn_sched_barrier(0);
+    load_used();
+  }
   // 2. hits and incoming rows, in active-list order
   int nj[JPT], pj[JPT];
-  uint32_t hi_cnt = 0;  // hits | incoming << 16
+  uint32_t cnt = 0;  // hits | incoming << 16
 #pragma unroll
   for (int q = 0; q < JPT; ++q) {
     const int j = tid * JPT + q;
-    nj[q] = ids[min(j, na > 0 ? na - 1 : 0)];
+    nj[q] = s.ids[min(j, na > 0 ? na - 1 : 0)];
     pj[q] = s.slot[na > 0 ? nj[q] : 0];
-    if (j < na) hi_cnt += pj[q] >= 0 ? 1u : 0x10000u;
+    if (j < na) cnt += pj[q] >= 0 ? 1u : 0x10000u;
   }
   uint32_t tot;
-  const uint32_t before = block_excl_scan_once<SD_NT>(hi_cnt, s.scan[1], &tot);
+  const uint32_t before = block_excl_scan_once<NT>(cnt, s.scan[1], &tot);
   if (s.bad || s.used != s.valid) return false;  // uniform
   const uint32_t nH = tot & 0xFFFFu, nI = tot >> 16;
   const uint32_t m = nI > s.nfree ? nI - s.nfree : 0u;
@@ -683,16 +650,19 @@ __device__ inline bool delta_fast(int l, int32_t token, const uint16_t* ids, int
   //    id) -- the largest keys ~last_used, ties to lower ids; their slots join
   //    the free ones
   if (m > 0) {
-    const int word = KPT == 32 ? tid : tid >> 1;
-    uint32_t cm = KPT * tid < F ? s.rmask[word] & ~s.amask[word] : 0u;
-    if constexpr (KPT == 16) cm = (cm >> (16 * (tid & 1))) & 0xFFFFu;
+    const uint32_t cw = lane < 2 * KPT ? s.rmask[2 * KPT * wave_id() + lane] &
+                                             ~s.amask[2 * KPT * wave_id() + lane]
+                                       : 0u;
     uint32_t mx = 0;
     bool odd = false;
 #pragma unroll
-    for (int b = 0; b < KPT; ++b) {
-      key[0][b] = ((cm >> b) & 1u) ? ~key[0][b] : 0u;
-      odd |= ((cm >> b) & 1u) && key[0][b] == 0u;  // resident and never used
-      mx = key[0][b] > mx ? key[0][b] : mx;
+    for (int r = 0; r < KPT; ++r) {
+      const uint64_t row = (uint32_t)__builtin_amdgcn_readlane((int)cw, 2 * r) |
+                           ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)cw, 2 * r + 1) << 32);
+      const bool cand = __builtin_amdgcn_inverse_ballot_w64(row);
+      odd |= cand && key[0][r] == 0xFFFFFFFFu;  // resident and never used
+      key[0][r] = cand ? ~key[0][r] : 0u;
+      mx = key[0][r] > mx ? key[0][r] : mx;
     }
     mx = wave_max(mx);
     if (lane == 0 && mx) atomicMax(&s.vmax, mx);
@@ -700,67 +670,61 @@ __device__ inline bool delta_fast(int l, int32_t token, const uint16_t* ids, int
     lds_barrier();
     if (s.bad) return false;  // uniform; nothing is written yet
     mx = s.vmax;
-    // ages from the oldest candidate's: bin 0 is the oldest token
+    // ages from the oldest candidate's token on, one bin each; the oldest
+    // SD_AGES of them nearly always hold m rows
 #pragma unroll
-    for (int b = 0; b < KPT; ++b) {
-      const uint32_t d = mx - key[0][b];
-      if (key[0][b] != 0u && d < (uint32_t)SD_BINS) {
-        atomicAdd(&s.vhist[d], 1u);
-        atomicAdd(&s.vcoarse[d / (SD_BINS / SD_COARSE)], 1u);
-      }
+    for (int r = 0; r < KPT; ++r) {
+      const uint32_t d = mx - key[0][r];
+      if (key[0][r] != 0u && d < (uint32_t)SD_AGES) atomicAdd(&s.vhist[d], 1u);
     }
     lds_barrier();
-    uint32_t vsel, vpos, bin, bef, cnt;
-    if (find_bin(s.vhist, s.vcoarse, m, &bin, &bef, &cnt)) {
-      uint32_t older = 0, eq = 0;
-#pragma unroll
-      for (int b = 0; b < KPT; ++b) {
-        const uint32_t d = mx - key[0][b];
-        older |= (key[0][b] != 0u && d < bin ? 1u : 0u) << b;
-        eq |= (key[0][b] != 0u && d == bin ? 1u : 0u) << b;
-      }
-      // one prefix sum places both: all older ones, the first m - bef equal
-      const uint32_t take = m - bef;
-      uint32_t t2;
-      const uint32_t pre = block_excl_scan_once<SD_NT>(
-          (uint32_t)__builtin_popcount(older) | ((uint32_t)__builtin_popcount(eq) << 16), s.scan[2],
-          &t2);
-      uint32_t ne = pre >> 16;
-      vpos = (pre & 0xFFFFu) + (ne < take ? ne : take);
-      vsel = older;
-      while (eq && ne < take) {
-        vsel |= eq & (0u - eq);
-        eq &= eq - 1;
-        ++ne;
-      }
-    } else {  // the oldest m span more than SD_BINS tokens
-      uint32_t sel[1];
+    uint32_t kth, take;
+    const uint32_t ages = wave_incl_scan(s.vhist[lane]);
+    const uint64_t hit = __ballot(ages >= m);
+    if (hit) {
+      const int at = __builtin_ctzll(hit);
+      take = m - (at > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)ages, at > 0 ? at - 1 : 0) : 0u);
+      kth = mx - (uint32_t)at;
+    } else {
       __syncthreads();
-      block_select_largest<SD_NT, 1>(key, m, sel, work, work + 4096, work + 4096 + 3 * SD_NW + 1);
-      vsel = sel[0];
-      uint32_t t2;
-      vpos = block_excl_scan_once<SD_NT>(__builtin_popcount(vsel), s.scan[2], &t2);
+      kth = block_find_kth<NT, 1>(key, m, &take, work, work + 4096, work + 4096 + 3 * S::NW + 1);
     }
-    while (vsel) {
-      const int n = KPT * tid + __builtin_ctz(vsel), old = s.slot[n];
-      vsel &= vsel - 1;
-      out.ev_ids[lo + vpos] = n;
+    // all older ones and the first `take` equal ones in id order; one prefix
+    // sum places both
+    store_rows<KPT>(s.gmask, [&](int r) { return key[0][r] > kth; });
+    store_rows<KPT>(s.emask, [&](int r) { return key[0][r] == kth; });
+    lds_barrier();
+    uint32_t v = tid < S::WORDS ? s.gmask[tid] : 0u, eq = tid < S::WORDS ? s.emask[tid] : 0u, t2;
+    const uint32_t pre = block_excl_scan_once<NT>(
+        (uint32_t)__builtin_popcount(v) | ((uint32_t)__builtin_popcount(eq) << 16), s.scan[2], &t2);
+    uint32_t ne = pre >> 16, vpos = (pre & 0xFFFFu) + (ne < take ? ne : take);
+    while (eq && ne < take) {
+      v |= eq & (0u - eq);
+      eq &= eq - 1;
+      ++ne;
+    }
+    while (v) {
+      const int id = 32 * tid + __builtin_ctz(v), old = s.slot[id];
+      v &= v - 1;
+      out.ev_ids[lo + vpos] = id;
       out.ev_slots[lo + vpos] = old;
       ++vpos;
       atomicOr(&s.smask[old >> 5], 1u << (old & 31));
       Q[old] = -1;
-      P[n] = -1;
+      P[id] = -1;
     }
     lds_barrier();
   }
   // 4. the slot pool in ascending order: its first nI slots go to the
-  //    incoming rows (ascending ids)
+  //    incoming rows (ascending ids); 8 to 32 slots a thread
   {
-    uint32_t bits = 32 * tid < C ? s.smask[tid] : 0u;
+    const int per = C <= 8 * NT ? 8 : (C <= 16 * NT ? 16 : 32);
+    uint32_t bits = per * tid < C ? (s.smask[(per * tid) >> 5] >> ((per * tid) & 31)) : 0u;
+    if (per < 32) bits &= (1u << per) - 1u;
     uint32_t st;
-    uint32_t pos = block_excl_scan_once<SD_NT>(__builtin_popcount(bits), s.scan[3], &st);
+    uint32_t pos = block_excl_scan_once<NT>(__builtin_popcount(bits), s.scan[3], &st);
     while (bits && pos < nI) {
-      const int sl = 32 * tid + __builtin_ctz(bits);
+      const int sl = per * tid + __builtin_ctz(bits);
       bits &= bits - 1;
       out.in_slots[lo + pos] = sl;
       s.pool[pos] = (uint16_t)sl;
@@ -785,6 +749,7 @@ __device__ inline bool delta_fast(int l, int32_t token, const uint16_t* ids, int
         Q[slot] = n;
       }
       U[n] = token;
+      if (ids_out) ids_out[j] = n;
       out.active_slots[lo + j] = slot;
     }
   }
@@ -802,11 +767,12 @@ __device__ inline bool delta_fast(int l, int32_t token, const uint16_t* ids, int
 // entry by entry from memory with every check, in few registers so that it
 // costs the fast path none.  Thread t owns id word t, slot word t and actives
 // [t*jpt, t*jpt+jpt).
+template <int NT>
 __device__ inline void delta_checked(int l, int32_t token, const int32_t* A, int na,
                                      bool bad_count, int32_t* P, int32_t* Q, int32_t* U,
                                      const np_delta_out& out, int F, int C, int k, void* ws,
                                      SdChecked& g) {
-  const int tid = threadIdx.x, jpt = (k + SD_NT - 1) / SD_NT;
+  const int tid = threadIdx.x, jpt = (k + NT - 1) / NT;
   const size_t lo = (size_t)l * k;
   const int j0 = min(tid * jpt, na), j1 = min(tid * jpt + jpt, na);
   __syncthreads();  // every thread is done with the LDS of the fast path
@@ -832,7 +798,7 @@ __device__ inline void delta_checked(int l, int32_t token, const int32_t* A, int
     cnt += p >= 0 ? 1u : 0x10000u;
   }
   uint32_t tot;
-  const uint32_t before = block_excl_scan<SD_NT>(cnt, g.scan, &tot);
+  const uint32_t before = block_excl_scan<NT>(cnt, g.scan, &tot);
   const uint32_t nH = tot & 0xFFFFu, nI = tot >> 16;
   uint32_t bits = 0;
 #pragma unroll 1
@@ -844,7 +810,7 @@ __device__ inline void delta_checked(int l, int32_t token, const int32_t* A, int
   }
   g.smask[tid] = bits;
   uint32_t nfree;
-  (void)block_excl_scan<SD_NT>(__builtin_popcount(bits), g.scan, &nfree);
+  (void)block_excl_scan<NT>(__builtin_popcount(bits), g.scan, &nfree);
   const uint32_t m = nI > nfree ? nI - nfree : 0u;
   if (m > 0) {  // the m largest keys ~last_used of the resident, non-active rows
     const uint32_t cm = g.rmask[tid] & ~g.amask[tid];
@@ -852,7 +818,7 @@ __device__ inline void delta_checked(int l, int32_t token, const int32_t* A, int
     uint32_t nz = 0;
 #pragma unroll 1
     for (int b = 0; b < 32; ++b) nz += key(b) != 0u;
-    (void)block_excl_scan<SD_NT>(nz, g.scan, &nz);
+    (void)block_excl_scan<NT>(nz, g.scan, &nz);
     uint32_t prefix = 0, pmask = 0, rem = m >= nz ? m - nz : m;
     if (m < nz) {
 #pragma unroll 1
@@ -880,13 +846,13 @@ __device__ inline void delta_checked(int l, int32_t token, const int32_t* A, int
       eq |= (kv == prefix ? 1u : 0u) << b;
     }
     uint32_t t2;
-    uint32_t ne = block_excl_scan<SD_NT>(__builtin_popcount(eq), g.scan, &t2);
+    uint32_t ne = block_excl_scan<NT>(__builtin_popcount(eq), g.scan, &t2);
     while (eq && ne < rem) {
       vsel |= eq & (0u - eq);
       eq &= eq - 1;
       ++ne;
     }
-    uint32_t vpos = block_excl_scan<SD_NT>(__builtin_popcount(vsel), g.scan, &t2);
+    uint32_t vpos = block_excl_scan<NT>(__builtin_popcount(vsel), g.scan, &t2);
 #pragma unroll 1
     while (vsel) {
       const int n = 32 * tid + __builtin_ctz(vsel), old = P[min(n, F - 1)];
@@ -906,7 +872,7 @@ __device__ inline void delta_checked(int l, int32_t token, const int32_t* A, int
   __syncthreads();
   bits = g.smask[tid];
   uint32_t st;
-  uint32_t pos = block_excl_scan<SD_NT>(__builtin_popcount(bits), g.scan, &st);
+  uint32_t pos = block_excl_scan<NT>(__builtin_popcount(bits), g.scan, &st);
   const uint32_t given = st < nI ? st : nI;  // slots actually handed out
 #pragma unroll 1
   while (bits && pos < nI) {
@@ -948,25 +914,27 @@ __device__ inline void delta_checked(int l, int32_t token, const int32_t* A, int
 }
 
 // np_delta and np_delta_n with the slot map in LDS.  Ids that are not
-// strictly ascending neuron ids go to the general delta, as does an
-// inconsistent slot map.
-template <int KPT, int CPT, int JPT, bool V4>
-__global__ __launch_bounds__(SD_NT) void delta_lds_kernel(
+// strictly ascending neuron ids go to delta_checked, as does an inconsistent
+// slot map.
+template <class S>
+__global__ __launch_bounds__(S::NT) void delta_lds_kernel(
     int32_t token, const int32_t* __restrict__ active_ids, int32_t* __restrict__ slot_of,
     int32_t* __restrict__ neuron_of, int32_t* __restrict__ last_used, np_delta_out out, int F,
     int C, int k, void* ws, const int32_t* __restrict__ counts) {
-  __shared__ __attribute__((aligned(16))) SdShared<KPT> sh;
-  __shared__ uint16_t ids_s[SD_MAX_K];
-  __shared__ uint32_t work[4096 + 3 * SD_NW + 1 + 4];
-  SdLds<KPT>& s = sh.f;
+  __shared__ __attribute__((aligned(16))) SdShared<S> sh;
+  __shared__ uint32_t work[4096 + 3 * S::NW + 1 + 4];
+  constexpr int KPT = S::KPT, CPT = S::CPT, JPT = S::JPT, NT = S::NT;
+  SdLds<S>& s = sh.f;
   const int l = blockIdx.x, tid = threadIdx.x;
   if (token == NP_TOKEN_AUTO) token = *(const int32_t*)((const char*)ws + WS_TOKEN);
   int32_t* P = slot_of + (size_t)l * F;
   int32_t* Q = neuron_of + (size_t)l * C;
   int32_t* U = last_used + (size_t)l * F;
   const int32_t* A = active_ids + (size_t)l * k;
-  SlotLoads<KPT, V4> p;
-  p.load(P, F);
+  uint32_t pv[KPT];
+  const RowLoads slot_rows(P, F, sd_id<KPT>(0));
+#pragma unroll
+  for (int r = 0; r < KPT; ++r) pv[r] = slot_rows.at(r);
   int na = k;  // active neurons of this layer: k, or a device count in [0, k]
   bool bad_count = false;
   if (counts) {
@@ -979,34 +947,34 @@ __global__ __launch_bounds__(SD_NT) void delta_lds_kernel(
   int id[JPT], prev[JPT];
 #pragma unroll
   for (int q = 0; q < JPT; ++q) {
-    const int j = min(tid + SD_NT * q, k - 1);
+    const int j = min(tid + NT * q, k - 1);
     id[q] = A[j];
     prev[q] = A[j > 0 ? j - 1 : 0];
   }
   int qv[CPT];
 #pragma unroll
-  for (int i = 0; i < CPT; ++i) qv[i] = Q[min(tid + SD_NT * i, C - 1)];
+  for (int i = 0; i < CPT; ++i) qv[i] = Q[min(tid + NT * i, C - 1)];
   sd_clear(s);
-  for (int i = tid; i < KPT * SD_NT / 32; i += SD_NT) s.amask[i] = 0u;
+  if (tid < S::WORDS) s.amask[tid] = 0u;
   lds_barrier();
-  p.store(s, F, C);
+  store_slots<S>(pv, s, F, C);
 #pragma unroll
   for (int q = 0; q < JPT; ++q) {
-    const int j = tid + SD_NT * q;
+    const int j = tid + NT * q;
     if (j < na) {
       const bool ok = id[q] >= 0 && id[q] < F && (j == 0 || id[q] > prev[q]);
       if (ok) {
-        ids_s[j] = (uint16_t)id[q];
+        s.ids[j] = (uint16_t)id[q];
         atomicOr(&s.amask[id[q] >> 5], 1u << (id[q] & 31));
       } else {
-        ids_s[j] = 0;
+        s.ids[j] = 0;
         s.bad = 1u;
       }
     }
   }
   lds_barrier();
-  if (!delta_fast<KPT, CPT, JPT, V4>(l, token, ids_s, na, qv, P, Q, U, out, F, C, k, s, work))
-    delta_checked(l, token, A, na, bad_count, P, Q, U, out, F, C, k, ws, sh.g);
+  if (!delta_fast<S>(l, token, na, qv, P, Q, U, nullptr, out, F, C, k, s, work))
+    delta_checked<NT>(l, token, A, na, bad_count, P, Q, U, out, F, C, k, ws, sh.g);
   else if (bad_count && tid == 0)
     raise_error(ws, NP_DEVERR_STATE);
 }
@@ -1048,18 +1016,18 @@ __global__ __launch_bounds__(NT) void delta_kernel(int32_t token,
 }
 
 // np_select followed by np_delta in one workgroup per layer.  At entry every
-// thread issues its loads at once: a share of slot_of, the scores of its ids
-// (the selection keys) and a share of neuron_of.
-template <int KPT, int CPT, int JPT, bool V4>
-__global__ __launch_bounds__(SD_NT) void select_delta_kernel(
+// thread issues its loads at once: slot_of and the scores (the selection keys)
+// of its ids and a share of neuron_of.
+template <class S>
+__global__ __launch_bounds__(S::NT) void select_delta_kernel(
     const float* __restrict__ scores, uint32_t* __restrict__ mask,
     int32_t* __restrict__ active_ids, int32_t token, int32_t* __restrict__ slot_of,
     int32_t* __restrict__ neuron_of, int32_t* __restrict__ last_used, np_delta_out out, int F,
     int C, int k, void* ws) {
-  __shared__ __attribute__((aligned(16))) SdShared<KPT> sh;
-  __shared__ uint16_t ids_s[SD_MAX_K];
-  __shared__ uint32_t work[4096 + 3 * SD_NW + 1 + 4];
-  SdLds<KPT>& s = sh.f;
+  __shared__ __attribute__((aligned(16))) SdShared<S> sh;
+  __shared__ uint32_t work[4096 + 3 * S::NW + 1 + 4];
+  constexpr int KPT = S::KPT, CPT = S::CPT, NT = S::NT;
+  SdLds<S>& s = sh.f;
   const int l = blockIdx.x, tid = threadIdx.x;
   if (token == NP_TOKEN_AUTO) token = *(const int32_t*)((const char*)ws + WS_TOKEN);
   const int words = (F + 31) / 32;
@@ -1067,71 +1035,50 @@ __global__ __launch_bounds__(SD_NT) void select_delta_kernel(
   int32_t* Q = neuron_of + (size_t)l * C;
   int32_t* U = last_used + (size_t)l * F;
   const float* sc = scores + (size_t)l * F;
-  SlotLoads<KPT, V4> p;
-  p.load(P, F);
+  uint32_t pv[KPT], key[1][KPT];
+  const RowLoads slot_rows(P, F, sd_id<KPT>(0)), score_rows(sc, F, sd_id<KPT>(0));
+#pragma unroll
+  for (int r = 0; r < KPT; ++r) pv[r] = slot_rows.at(r);
+#pragma unroll
+  for (int r = 0; r < KPT; ++r) key[0][r] = score_rows.at(r);
+  uint32_t* hint = l < WS_SEL_HINT_LAYERS ? (uint32_t*)((char*)ws + WS_SEL_HINT) + 2 * l : nullptr;
+  const uint32_t hkey = hint ? hint[0] : 0u, half = hint ? hint[1] : 0u;
   sd_clear(s);
   lds_barrier();
-  // (wide unaligned layers: slot_of first, both would not fit the registers)
-  constexpr bool P_FIRST = !V4 && KPT == 32;
-  if constexpr (P_FIRST) p.store(s, F, C);
-  uint32_t key[1][KPT];
+  store_slots<S>(pv, s, F, C);
   bool nan = false;
-  if (KPT * tid < F) {
-    float v[KPT];
-    if constexpr (V4) {
-      const int last = F / 4 - 1;
 #pragma unroll
-      for (int i = 0; i < KPT / 4; ++i) {
-        const float4 q = reinterpret_cast<const float4*>(sc)[min(KPT / 4 * tid + i, last)];
-        v[4 * i] = q.x;
-        v[4 * i + 1] = q.y;
-        v[4 * i + 2] = q.z;
-        v[4 * i + 3] = q.w;
-      }
-    } else {
-#pragma unroll
-      for (int b = 0; b < KPT; ++b) v[b] = sc[min(KPT * tid + b, F - 1)];
-    }
-#pragma unroll
-    for (int b = 0; b < KPT; ++b) {
-      const uint32_t kv = score_key(v[b], &nan);
-      key[0][b] = KPT * tid + b < F ? kv : 0u;
-    }
-  } else {
-#pragma unroll
-    for (int b = 0; b < KPT; ++b) key[0][b] = 0u;
+  for (int r = 0; r < KPT; ++r) {
+    const uint32_t kv = score_key(__uint_as_float(key[0][r]), &nan);
+    key[0][r] = sd_id<KPT>(r) < F ? kv : 0u;
   }
-  int qv[CPT];
-#pragma unroll
-  for (int i = 0; i < CPT; ++i) qv[i] = Q[min(tid + SD_NT * i, C - 1)];
-  if constexpr (!P_FIRST) p.store(s, F, C);
   if (nan) raise_error(ws, NP_DEVERR_NAN_SCORE);
-  uint32_t* hint = l < WS_SEL_HINT_LAYERS ? (uint32_t*)((char*)ws + WS_SEL_HINT) + 2 * l : nullptr;
-  uint32_t sel = select_hinted<KPT>(key, (uint32_t)k, s, work, hint);
+  int qv[CPT];  // behind the selection where the registers do not hold both
+  auto load_q = [&] {
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) qv[i] = Q[min(tid + NT * i, C - 1)];
+  };
+  if constexpr (KPT < 32) load_q();
+  select_hinted<S>(key, (uint32_t)k, s, work, hint, hkey, half);
+  if constexpr (KPT == 32) load_q();
   {  // the mask, and the ids in ascending order
-    const uint32_t ww = whole_word<KPT>(sel);
-    const int word = KPT == 32 ? tid : tid >> 1;
-    if (KPT == 32 || (tid & 1) == 0) {
-      s.amask[word] = ww;
-      if (word < words) mask[(size_t)l * words + word] = ww;
-    }
-    uint32_t tot;
-    uint32_t pos = block_excl_scan_once<SD_NT>(__builtin_popcount(sel), s.scan[4], &tot);
+    uint32_t sel = tid < S::WORDS ? s.amask[tid] : 0u, tot;
+    if (tid < words) mask[(size_t)l * words + tid] = sel;
+    uint32_t pos = block_excl_scan_once<NT>(__builtin_popcount(sel), s.scan[4], &tot);
     while (sel) {
-      const int n = KPT * tid + __builtin_ctz(sel);
+      const int n = 32 * tid + __builtin_ctz(sel);
       sel &= sel - 1;
-      if (pos < (uint32_t)k) {
-        active_ids[(size_t)l * k + pos] = n;
-        ids_s[pos] = (uint16_t)n;
-      }
+      if (pos < (uint32_t)k) s.ids[pos] = (uint16_t)n;
       ++pos;
     }
   }
-  lds_barrier();  // ids_s, s.slot and the masks complete
-  if (!delta_fast<KPT, CPT, JPT, V4>(l, token, ids_s, k, qv, P, Q, U, out, F, C, k, s, work)) {
+  lds_barrier();  // s.ids complete
+  int32_t* ids_out = active_ids + (size_t)l * k;
+  if (!delta_fast<S>(l, token, k, qv, P, Q, U, ids_out, out, F, C, k, s, work)) {
+    for (int j = tid; j < k; j += NT) ids_out[j] = s.ids[j];
     __syncthreads();
     __threadfence_block();  // the ids are read back from memory
-    delta_checked(l, token, active_ids + (size_t)l * k, k, false, P, Q, U, out, F, C, k, ws, sh.g);
+    delta_checked<NT>(l, token, ids_out, k, false, P, Q, U, out, F, C, k, ws, sh.g);
   }
 }
 
@@ -1300,23 +1247,17 @@ static bool fits_lds(const np_shape& s) {
   return s.d_ffn <= SD_MAX_F && s.capacity <= SD_MAX_C && s.k <= SD_MAX_K;
 }
 
-// Calls f with the sizes of the LDS kernels for this shape: ids, slots and
-// active rows per thread.  Half as many ids per thread keep all 16 waves busy
-// where F allows it.
+// Calls f with the smallest build of the LDS kernels that holds this shape: 8
+// waves for small layers, 16 from there on (7B, in-kernel: 12.2 us with 16
+// waves of 12 rows, 14.8 with 8 of 24).
 template <class Fn>
 static void with_sd_sizes(const np_shape& s, Fn f) {
-  const int jpt = (s.k + SD_NT - 1) / SD_NT;
-  auto j = [&](auto kpt, auto cpt) {
-    if (jpt <= 2) f(kpt, cpt, std::integral_constant<int, 2>());
-    else if (jpt <= 4) f(kpt, cpt, std::integral_constant<int, 4>());
-    else f(kpt, cpt, std::integral_constant<int, 8>());
-  };
-  if (s.d_ffn <= 16 * SD_NT) {
-    if (s.capacity <= 8 * SD_NT) j(std::integral_constant<int, 16>(), std::integral_constant<int, 8>());
-    else j(std::integral_constant<int, 16>(), std::integral_constant<int, 16>());
-  } else {
-    j(std::integral_constant<int, 32>(), std::integral_constant<int, 16>());
-  }
+  if (s.d_ffn <= 4096 && s.k <= 2048) f(Sd<512, 8, 8, 4>());
+  else if (s.d_ffn <= 12288 && s.capacity <= 8192 && s.k <= 2048) f(Sd<1024, 12, 8, 2>());
+  else if (s.d_ffn <= 16384 && s.k <= 2048) f(Sd<1024, 16, 16, 2>());
+  else if (s.d_ffn <= 16384) f(Sd<1024, 16, 16, 8>());
+  else if (s.k <= 4096) f(Sd<1024, 32, 16, 4>());
+  else f(Sd<1024, 32, 16, 8>());
 }
 
 static hipError_t advance_token(int32_t token, void* ws, hipStream_t stream) {
@@ -1330,16 +1271,11 @@ hipError_t launch_delta(const np_shape& s, int32_t token, const int32_t* active_
                         const np_state& st, const np_delta_out& out, void* ws,
                         hipStream_t stream, const int32_t* counts) {
   if (fits_lds(s)) {
-    with_sd_sizes(s, [&](auto kpt, auto cpt, auto jpt) {
-      constexpr int K = decltype(kpt)::value, C = decltype(cpt)::value, J = decltype(jpt)::value;
-      if (s.d_ffn % 4 == 0)
-        hipLaunchKernelGGL((delta_lds_kernel<K, C, J, true>), dim3(s.layers), dim3(SD_NT), 0,
-                           stream, token, active_ids, st.slot_of, st.neuron_of, st.last_used, out,
-                           s.d_ffn, s.capacity, s.k, ws, counts);
-      else
-        hipLaunchKernelGGL((delta_lds_kernel<K, C, J, false>), dim3(s.layers), dim3(SD_NT), 0,
-                           stream, token, active_ids, st.slot_of, st.neuron_of, st.last_used, out,
-                           s.d_ffn, s.capacity, s.k, ws, counts);
+    with_sd_sizes(s, [&](auto z) {
+      using S = decltype(z);
+      hipLaunchKernelGGL((delta_lds_kernel<S>), dim3(s.layers), dim3(S::NT), 0, stream, token,
+                         active_ids, st.slot_of, st.neuron_of, st.last_used, out, s.d_ffn,
+                         s.capacity, s.k, ws, counts);
     });
     return advance_token(token, ws, stream);
   }
@@ -1360,16 +1296,11 @@ hipError_t launch_select_delta(const np_shape& s, int32_t token, const float* sc
     if (e != hipSuccess) return e;
     return launch_delta(s, token, active_ids, st, out, ws, stream, nullptr);
   }
-  with_sd_sizes(s, [&](auto kpt, auto cpt, auto jpt) {
-    constexpr int K = decltype(kpt)::value, C = decltype(cpt)::value, J = decltype(jpt)::value;
-    if (s.d_ffn % 4 == 0)
-      hipLaunchKernelGGL((select_delta_kernel<K, C, J, true>), dim3(s.layers), dim3(SD_NT), 0,
-                         stream, scores, mask, active_ids, token, st.slot_of, st.neuron_of,
-                         st.last_used, out, s.d_ffn, s.capacity, s.k, ws);
-    else
-      hipLaunchKernelGGL((select_delta_kernel<K, C, J, false>), dim3(s.layers), dim3(SD_NT), 0,
-                         stream, scores, mask, active_ids, token, st.slot_of, st.neuron_of,
-                         st.last_used, out, s.d_ffn, s.capacity, s.k, ws);
+  with_sd_sizes(s, [&](auto z) {
+    using S = decltype(z);
+    hipLaunchKernelGGL((select_delta_kernel<S>), dim3(s.layers), dim3(S::NT), 0, stream, scores,
+                       mask, active_ids, token, st.slot_of, st.neuron_of, st.last_used, out,
+                       s.d_ffn, s.capacity, s.k, ws);
   });
   return advance_token(token, ws, stream);
 }
