@@ -36,10 +36,12 @@ namespace np {
 //
 // Two regimes.  Up to 128 tokens it is HBM-bound (n flops per weight byte):
 // small blocks, so that all CUs stream, long pieces (fewer barriers), the
-// nontemporal hint on weights that one block reads.  SwiGLU 7B layer (14336 x
-// 4096 f16, 235 MB of weights), 128 tokens: 60.2 us, 64 tokens 48.4 us (a plain
-// read of the same rows 43.8 us); with 128-byte pieces 64 and 51; the
-// four-wave kernel before, whose loads the compiler had put behind the
+// nontemporal hint on weights that one block reads, and two groups of four
+// waves that take half of a piece's steps each, so that a wave's tiles are
+// twice as large and its operands read less often.  SwiGLU 7B layer (14336 x
+// 4096 f16, 235 MB of weights), 128 tokens: 58-60 us, 64 tokens 48-51 us (a
+// plain read of the same rows 43.8 us); with one group of eight waves 2-5%
+// more, with 128-byte pieces 64 and 51; the four-wave kernel before, whose loads the compiler had put behind the
 // products they were to overlap, 76.5 and 68.7.  Beyond, it is bound by the
 // matrix cores and by what feeds them: a 128 x 256 block reads 96 bytes of LDS
 // a cycle for 8 waves of 128 x 64 outputs, and each weight row once per 256
@@ -59,16 +61,17 @@ struct ActBatchArgs {
   int fb, tb;       // neuron blocks, token blocks
 };
 
-template <int MT_, int NT_, int WGM_, int WGN_, int DEPTH_, int ROWB_>
+template <int MT_, int NT_, int WGM_, int WGN_, int DEPTH_, int ROWB_, int KW_ = 1>
 struct AbTile {
   static constexpr int ROWB = ROWB_, PITCH = ROWB + 16;
   static constexpr int MT = MT_, NT = NT_, WGM = WGM_, WGN = WGN_, DEPTH = DEPTH_;
+  static constexpr int KW = KW_;  // groups of waves, each a share of a piece's steps
   static constexpr int BM = 16 * MT * WGM, BN = 16 * NT * WGN;
   static constexpr int ROWS = 2 * BM + BN;               // LDS rows: gate, up, tokens
   static constexpr int PIECES = ROWS * (ROWB / 16);   // 16-byte pieces of an iteration
   static constexpr int PPT = PIECES / AB_NT;             // per thread
   static constexpr size_t LDS = (size_t)2 * ROWS * PITCH;
-  static_assert(WGM * WGN == AB_WAVES && PIECES % AB_NT == 0 &&
+  static_assert(WGM * WGN * KW == AB_WAVES && ROWB / 64 % (2 * KW) == 0 && PIECES % AB_NT == 0 &&
                     2 * BM % (AB_NT / (ROWB / 16)) == 0,
                 "whole pieces per thread, weights and tokens in separate ones");
 };
@@ -81,7 +84,8 @@ __global__ __launch_bounds__(AB_NT) void act_batch_kernel(ActBatchArgs a) {
   constexpr int MT = C::MT, NT = C::NT, PPT = C::PPT, DEPTH = C::DEPTH;
   __shared__ __attribute__((aligned(16))) char ab_lds[C::LDS];
   const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE, grp = lane / 16, li = lane & 15;
-  const int wm = w / C::WGN, wn = w % C::WGN;
+  constexpr int KW = C::KW, STEPS = ROWB / 64 / KW;  // steps of a piece for each wave
+  const int kg = w / (C::WGM * C::WGN), wm = w / C::WGN % C::WGM, wn = w % C::WGN;
   // blocks b, b + 8, ... run on one XCD: each XCD takes a contiguous run of
   // blocks, token blocks innermost, so its L2 serves a weight panel to the
   // token blocks that share it
@@ -132,8 +136,9 @@ __global__ __launch_bounds__(AB_NT) void act_batch_kernel(ActBatchArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) accg[m][j][r] = accu[m][j][r] = 0.f;
   // fragment addresses: gate rows of this wave's first tile, tokens likewise
-  const char* const fg = ab_lds + (size_t)(wm * MT * 16 + li) * PITCH + grp * 16;
-  const char* const fx = ab_lds + (size_t)(2 * C::BM + wn * NT * 16 + li) * PITCH + grp * 16;
+  const char* const fg = ab_lds + (size_t)(wm * MT * 16 + li) * PITCH + kg * STEPS * 64 + grp * 16;
+  const char* const fx = ab_lds + (size_t)(2 * C::BM + wn * NT * 16 + li) * PITCH + kg * STEPS * 64 +
+                         grp * 16;
   auto multiply = [&](int buf, int s_begin, int s_end) {
     const size_t bo = (size_t)buf * C::ROWS * PITCH;
 #pragma unroll
@@ -165,16 +170,45 @@ __global__ __launch_bounds__(AB_NT) void act_batch_kernel(ActBatchArgs a) {
 #pragma unroll
     for (int q = 0; q < 2 * DEPTH; ++q) {
       store((q + 1) & 1, pre[q % DEPTH]);
-      multiply(q & 1, 0, ROWB / 128);
+      multiply(q & 1, 0, STEPS / 2);
       __builtin_amdgcn_sched_barrier(0);  // neither ahead of the stores nor behind the products
       load(it + q + 1 + DEPTH, pre[q % DEPTH]);
       __builtin_amdgcn_sched_barrier(0);
-      multiply(q & 1, ROWB / 128, ROWB / 64);
+      multiply(q & 1, STEPS / 2, STEPS);
       if (it + q + 1 >= iters) goto done;  // (a skipped iteration would blur the load counts)
       lds_barrier();
     }
   }
 done:
+  if constexpr (KW > 1) {  // the other groups' sums join group 0's, in order
+    static_assert((size_t)(KW - 1) * C::BM * C::BN * 8 <= C::LDS, "the sums fit the pieces' LDS");
+    f32x4* sums = reinterpret_cast<f32x4*>(ab_lds);
+    const int slot = (w % (C::WGM * C::WGN)) * MT * NT * 2;
+    __syncthreads();  // every wave is done with the pieces
+    if (kg > 0) {
+      f32x4* p = sums + (size_t)(kg - 1) * C::WGM * C::WGN * MT * NT * 2 * WAVE + lane;
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          p[(size_t)(slot + 2 * (m * NT + j)) * WAVE] = accg[m][j];
+          p[(size_t)(slot + 2 * (m * NT + j) + 1) * WAVE] = accu[m][j];
+        }
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int g = 0; g < KW - 1; ++g) {
+      const f32x4* p = sums + (size_t)g * C::WGM * C::WGN * MT * NT * 2 * WAVE + lane;
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          accg[m][j] += p[(size_t)(slot + 2 * (m * NT + j)) * WAVE];
+          accu[m][j] += p[(size_t)(slot + 2 * (m * NT + j) + 1) * WAVE];
+        }
+    }
+  }
   // acts[token][neuron]: lane l, register r holds neuron 16 m + 4 (l / 16) + r
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
@@ -223,7 +257,7 @@ static hipError_t act_batch_t(const np_shape& s, const void* weights, const void
   a.d = s.d_model;
   a.act = s.act;
   // The block whose rounds over the 256 CUs cost least: the time of a round
-  // of each block, relative to each other (d 4096: 119, 74, 51 and 33 us in
+  // of each block, relative to each other (d 4096: 119, 74, 48 and 32 us in
   // f16; fp32 is bound by its matrix rate and goes by the area alone), is the
   // same for any size within 10%: f16, n = 256, F = 14336, one round of 128 x
   // 128 takes 84 us, one of 128 x 256 115, two of 64 x 128 97; n = 1500, d 600,
@@ -233,7 +267,7 @@ static hipError_t act_batch_t(const np_shape& s, const void* weights, const void
     float cost16, cost32;
   };
   static constexpr Block blocks[4] = {
-      {128, 256, 119.f, 6.4f}, {128, 128, 74.f, 3.3f}, {64, 128, 51.f, 1.8f}, {64, 64, 33.f, 1.f}};
+      {128, 256, 119.f, 6.4f}, {128, 128, 74.f, 3.3f}, {64, 128, 48.f, 1.8f}, {64, 64, 32.f, 1.f}};
   int best = 0;
   float least = 0.f;
   for (int i = 0; i < 4; ++i) {
@@ -251,11 +285,11 @@ static hipError_t act_batch_t(const np_shape& s, const void* weights, const void
     case 0: return launch_ab<T, AbTile<4, 4, 2, 4, 1, 128>, false>(a, stream);
     case 1: return launch_ab<T, AbTile<2, 4, 4, 2, 2, 128>, false>(a, stream);
     case 2:
-      return once ? launch_ab<T, AbTile<1, 4, 4, 2, 1, 256>, true>(a, stream)
-                  : launch_ab<T, AbTile<1, 4, 4, 2, 1, 256>, false>(a, stream);
+      return once ? launch_ab<T, AbTile<2, 4, 2, 2, 1, 256, 2>, true>(a, stream)
+                  : launch_ab<T, AbTile<2, 4, 2, 2, 1, 256, 2>, false>(a, stream);
     default:
-      return once ? launch_ab<T, AbTile<1, 2, 4, 2, 1, 256>, true>(a, stream)
-                  : launch_ab<T, AbTile<1, 2, 4, 2, 1, 256>, false>(a, stream);
+      return once ? launch_ab<T, AbTile<2, 2, 2, 2, 1, 256, 2>, true>(a, stream)
+                  : launch_ab<T, AbTile<2, 2, 2, 2, 1, 256, 2>, false>(a, stream);
   }
 }
 
