@@ -259,7 +259,7 @@ np_status np_delta(const np_shape* shape, int32_t token,
  * two calls, the same results bit for bit (mask, active_ids, the state and
  * every `out` list), the same error reporting (NP_DEVERR_NAN_SCORE,
  * NP_DEVERR_STATE).  Where the layer fits one workgroup's local memory
- * (F <= 16384, C <= 8192, k <= 4096) both steps run in one kernel per layer
+ * (F <= 32768, C <= 16384, k <= 8192) both steps run in one kernel per layer
  * that reads slot_of and neuron_of once into local memory at entry, together
  * with the scores; other shapes run np_select's and np_delta's kernels.  With
  * token == NP_TOKEN_AUTO a second kernel advances the step counter, as in
