@@ -352,7 +352,7 @@ __device__ inline void delta_layer(int l, int32_t token, const int32_t* A, int n
 // checked once, which frees every later step of its checks: an inconsistent
 // layer takes delta_checked.  7B, per token: 23.3 us with 512
 // threads of 32 ids and about 45 barriers; 70B: 22.3 + 21.2 us in two kernels
-// that read the state from memory.  The figures now are at the launch rule.
+// that read the state from memory.  Now: 7B 11.3 us (13.5 a call), 70B 22 (32 a call).
 // ---------------------------------------------------------------------------
 constexpr int SD_MAX_F = 32768;
 constexpr int SD_MAX_C = 16384;
