@@ -383,7 +383,8 @@ struct SdLds {
   alignas(16) uint32_t hist[SD_BINS];
   uint32_t vhist[SD_AGES];
   uint32_t cand[SD_CAND], scan[8][S::NW];
-  uint32_t above, ncand, vmax, used, valid, nfree, bad;
+  uint32_t above, ncand, vmax, used, valid, nfree;
+  uint32_t bad, odd;  // set before step 2's barrier; in step 3 only
 };
 // LDS of delta_checked, when the slot map is inconsistent
 struct SdChecked {
@@ -575,7 +576,7 @@ __device__ inline void sd_clear(SdLds<S>& s) {
   const int tid = threadIdx.x;
   if (tid < SD_BINS) s.hist[tid] = 0u;
   if (tid < SD_AGES) s.vhist[tid] = 0u;
-  if (tid == 0) s.above = s.ncand = s.vmax = s.used = s.valid = s.nfree = s.bad = 0u;
+  if (tid == 0) s.above = s.ncand = s.vmax = s.used = s.valid = s.nfree = s.bad = s.odd = 0u;
 }
 
 // The delta of one layer with a consistent slot map in LDS.  qv: this thread's
@@ -643,7 +644,9 @@ __device__ inline bool delta_fast(int l, int32_t token, int na, const int (&qv)[
   }
   uint32_t tot;
   const uint32_t before = block_excl_scan_once<NT>(cnt, s.scan[1], &tot);
-  if (s.bad || s.used != s.valid) return false;  // uniform
+  // uniform: nothing writes these words from the barrier on (a wave may read
+  // them while another is in step 3 already)
+  if (s.bad || s.used != s.valid) return false;
   const uint32_t nH = tot & 0xFFFFu, nI = tot >> 16;
   const uint32_t m = nI > s.nfree ? nI - s.nfree : 0u;
   // 3. victims: the m resident, non-active rows with the smallest (last_used,
@@ -666,9 +669,9 @@ __device__ inline bool delta_fast(int l, int32_t token, int na, const int (&qv)[
     }
     mx = wave_max(mx);
     if (lane == 0 && mx) atomicMax(&s.vmax, mx);
-    if (odd) s.bad = 1u;
+    if (odd) s.odd = 1u;
     lds_barrier();
-    if (s.bad) return false;  // uniform; nothing is written yet
+    if (s.odd) return false;  // uniform; nothing is written yet
     mx = s.vmax;
     // ages from the oldest candidate's token on, one bin each; the oldest
     // SD_AGES of them nearly always hold m rows
@@ -832,7 +835,7 @@ __device__ inline void delta_checked(int l, int32_t token, const int32_t* A, int
         }
         __syncthreads();
         uint32_t bin = 255;
-        while (g.hist[bin] < rem) rem -= g.hist[bin--];
+        while (bin > 0u && g.hist[bin] < rem) rem -= g.hist[bin--];
         prefix |= bin << shift;
         pmask |= 255u << shift;
         __syncthreads();

@@ -151,3 +151,82 @@ def test_delta_lds_bad_inputs(bad):
     assert np.all(lists["active_slots"] < C) and np.all(lists["active_slots"] >= -1)
     P, Q, _ = bufs.host_state()
     assert np.all(Q < F) and np.all(Q >= -1)
+
+
+# The same layers with F padded past 32768 run delta_kernel (delta_layer, the
+# state read from memory): the added ids are never active and never resident,
+# so every list and the unpadded part of the state must come out the same.
+PADDED_F = 33000
+
+
+class Pair:
+    """One state in the LDS kernels' shape and in the padded one."""
+
+    def __init__(self, shape, P, Q, U):
+        self.shape = L, F, k, C = shape
+        self.lds, self.gen = Bufs(cfg_of(L, F, k, C)), Bufs(cfg_of(L, PADDED_F, k, C))
+        for b, width in ((self.lds, F), (self.gen, PADDED_F)):
+            b.reset()
+            b.slot_of.view(L, width)[:, :F] = torch.from_numpy(P).cuda()
+            b.neuron_of.copy_(torch.from_numpy(Q).reshape(-1))
+            b.last_used.view(L, width)[:, :F] = torch.from_numpy(U).cuda()
+
+    def step(self, entry, token, ids, counts=None):
+        """One delta of the ids through `entry` on both; returns the lists and
+        the error word, having compared everything."""
+        L, F, k, C = self.shape
+        dev = torch.from_numpy(ids).cuda()
+        for b, width in ((self.lds, F), (self.gen, PADDED_F)):
+            if entry == "select_delta":
+                s = np.full((L, width), -1.0, np.float32)
+                for l in range(L):
+                    s[l, ids[l]] = 1.0 + ids[l] / np.float32(width)
+                B.np_select_delta(b.shape, token, torch.from_numpy(s).cuda(), b.mask, b.ids, b.state,
+                                  b.out, b.ws)
+            elif entry == "delta_n":
+                n = np.zeros(max(L, 4), np.int32)
+                n[:L] = k if counts is None else counts
+                B.np_delta_n(b.shape, token, dev, torch.from_numpy(n).cuda(), b.state, b.out, b.ws)
+            else:
+                B.np_delta(b.shape, token, dev, b.state, b.out, b.ws)
+        torch.cuda.synchronize()
+        got, ref = self.lds.host_lists(), self.gen.host_lists()
+        compare_delta(got, ref, L)
+        for x, y in zip(self.lds.host_state(), self.gen.host_state()):
+            w = x.shape[1]
+            assert np.array_equal(x, y[:, :w])
+            assert np.all(y[:, w:] == -1)
+        err = B.np_device_error(self.lds.ws)
+        assert err == B.np_device_error(self.gen.ws)
+        return got, err
+
+
+def seeded(rng, shape, resident, never, tokens):
+    """A consistent slot map with `resident` rows a layer, `never` of them
+    never used, the others last used at a token of [0, tokens)."""
+    L, F, k, C = shape
+    P, U = np.full((L, F), -1, np.int32), np.full((L, F), -1, np.int32)
+    Q = np.full((L, C), -1, np.int32)
+    for l in range(L):
+        n, s = rng.permutation(F)[:resident], rng.permutation(C)[:resident]
+        P[l, n], Q[l, s] = s, n
+        U[l, n[never:]] = rng.integers(0, tokens, resident - never)
+    return P, Q, U
+
+
+@pytest.mark.parametrize("entry", ["delta", "delta_n", "select_delta"])
+@pytest.mark.parametrize("tokens", [50, 4000])  # ages inside and past the histogram
+@pytest.mark.parametrize("shape", [(2, 3000, 300, 900), (2, 11008, 1651, 5504),
+                                   (1, 28672, 2867, 8601)], ids=lambda s: f"F{s[1]}")
+def test_delta_lds_never_used_rows(shape, tokens, entry):
+    """A slot map that the caller seeded, full but for a few slots, a tenth of
+    its rows never used (last_used -1)."""
+    L, F, k, C = shape
+    say(f"[delta lds never used] {shape} {tokens} {entry}")
+    rng = np.random.default_rng(C + tokens)
+    pair = Pair(shape, *seeded(rng, shape, C - 7, C // 10, tokens))
+    for i in range(3):
+        ids = np.stack([np.sort(rng.choice(F, k, replace=False)) for _ in range(L)]).astype(np.int32)
+        got, err = pair.step(entry, tokens + i, ids)
+        assert err == 0
+        assert np.all(got["counts"][:, 2] > 0)  # victims
