@@ -116,6 +116,14 @@ __global__ __launch_bounds__(NT) void select_kernel(const float* __restrict__ sc
                            active_ids + (size_t)l * k, nullptr, scan);
 }
 
+// Order of the victims as a selection key: the smallest last_used first, so
+// never (-1) has the largest key and a later token a smaller one; never 0,
+// which marks rows that are no candidates.
+__device__ inline uint32_t victim_key(uint32_t used) {
+  const uint32_t key = ~(used + 1u);
+  return key > 1u ? key : 1u;
+}
+
 // The delta of one layer, run by all NT threads of its workgroup, for any
 // state, also an inconsistent one.  Thread t owns: actives j in [t*JPT,
 // t*JPT+JPT), id words [t*WPT, t*WPT+WPT) and slot words [t*spt, t*spt+spt), so
@@ -220,7 +228,7 @@ __device__ inline void delta_layer(int l, int32_t token, const int32_t* A, int n
   const uint32_t m = nI > nfree ? nI - nfree : 0u;
 
   // 3. victims: the m resident, non-active rows with the smallest
-  //    (last_used, id) -- the largest keys ~last_used, ties to lower ids.
+  //    (last_used, id) -- the largest victim keys, ties to lower ids.
   //    Each victim leaves the slot map here: its slot joins the pool.
   uint32_t vsel[WPT];
 #pragma unroll
@@ -236,7 +244,7 @@ __device__ inline void delta_layer(int l, int32_t token, const int32_t* A, int n
         // resident, not active, and inside the layer (rmask has no bits past F)
         const uint32_t cm = word < idwords ? (rmask[word] & ~amask[word]) : 0u;
 #pragma unroll
-        for (int b = 0; b < 32; ++b) key[w][b] = ((cm >> b) & 1u) ? ~key[w][b] : 0u;
+        for (int b = 0; b < 32; ++b) key[w][b] = ((cm >> b) & 1u) ? victim_key(key[w][b]) : 0u;
       }
     } else {
 #pragma unroll
@@ -384,7 +392,7 @@ struct SdLds {
   uint32_t vhist[SD_AGES];
   uint32_t cand[SD_CAND], scan[8][S::NW];
   uint32_t above, ncand, vmax, used, valid, nfree;
-  uint32_t bad, odd;  // set before step 2's barrier; in step 3 only
+  uint32_t bad;  // set before step 2's barrier only
 };
 // LDS of delta_checked, when the slot map is inconsistent
 struct SdChecked {
@@ -576,7 +584,7 @@ __device__ inline void sd_clear(SdLds<S>& s) {
   const int tid = threadIdx.x;
   if (tid < SD_BINS) s.hist[tid] = 0u;
   if (tid < SD_AGES) s.vhist[tid] = 0u;
-  if (tid == 0) s.above = s.ncand = s.vmax = s.used = s.valid = s.nfree = s.bad = s.odd = 0u;
+  if (tid == 0) s.above = s.ncand = s.vmax = s.used = s.valid = s.nfree = s.bad = 0u;
 }
 
 // The delta of one layer with a consistent slot map in LDS.  qv: this thread's
@@ -650,28 +658,24 @@ __device__ inline bool delta_fast(int l, int32_t token, int na, const int (&qv)[
   const uint32_t nH = tot & 0xFFFFu, nI = tot >> 16;
   const uint32_t m = nI > s.nfree ? nI - s.nfree : 0u;
   // 3. victims: the m resident, non-active rows with the smallest (last_used,
-  //    id) -- the largest keys ~last_used, ties to lower ids; their slots join
-  //    the free ones
+  //    id) -- the largest victim keys, ties to lower ids; their slots join the
+  //    free ones (k <= C: a consistent map holds at least m candidates)
   if (m > 0) {
     const uint32_t cw = lane < 2 * KPT ? s.rmask[2 * KPT * wave_id() + lane] &
                                              ~s.amask[2 * KPT * wave_id() + lane]
                                        : 0u;
     uint32_t mx = 0;
-    bool odd = false;
 #pragma unroll
     for (int r = 0; r < KPT; ++r) {
       const uint64_t row = (uint32_t)__builtin_amdgcn_readlane((int)cw, 2 * r) |
                            ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)cw, 2 * r + 1) << 32);
       const bool cand = __builtin_amdgcn_inverse_ballot_w64(row);
-      odd |= cand && key[0][r] == 0xFFFFFFFFu;  // resident and never used
-      key[0][r] = cand ? ~key[0][r] : 0u;
+      key[0][r] = cand ? victim_key(key[0][r]) : 0u;
       mx = key[0][r] > mx ? key[0][r] : mx;
     }
     mx = wave_max(mx);
     if (lane == 0 && mx) atomicMax(&s.vmax, mx);
-    if (odd) s.odd = 1u;
     lds_barrier();
-    if (s.odd) return false;  // uniform; nothing is written yet
     mx = s.vmax;
     // ages from the oldest candidate's token on, one bin each; the oldest
     // SD_AGES of them nearly always hold m rows
@@ -815,9 +819,9 @@ __device__ inline void delta_checked(int l, int32_t token, const int32_t* A, int
   uint32_t nfree;
   (void)block_excl_scan<NT>(__builtin_popcount(bits), g.scan, &nfree);
   const uint32_t m = nI > nfree ? nI - nfree : 0u;
-  if (m > 0) {  // the m largest keys ~last_used of the resident, non-active rows
+  if (m > 0) {  // the m largest victim keys of the resident, non-active rows
     const uint32_t cm = g.rmask[tid] & ~g.amask[tid];
-    auto key = [&](int b) { return ((cm >> b) & 1u) ? ~(uint32_t)U[32 * tid + b] : 0u; };
+    auto key = [&](int b) { return ((cm >> b) & 1u) ? victim_key((uint32_t)U[32 * tid + b]) : 0u; };
     uint32_t nz = 0;
 #pragma unroll 1
     for (int b = 0; b < 32; ++b) nz += key(b) != 0u;

@@ -216,17 +216,24 @@ def seeded(rng, shape, resident, never, tokens):
 
 @pytest.mark.parametrize("entry", ["delta", "delta_n", "select_delta"])
 @pytest.mark.parametrize("tokens", [50, 4000])  # ages inside and past the histogram
+@pytest.mark.parametrize("never", [0.1, 1.0])
 @pytest.mark.parametrize("shape", [(2, 3000, 300, 900), (2, 11008, 1651, 5504),
                                    (1, 28672, 2867, 8601)], ids=lambda s: f"F{s[1]}")
-def test_delta_lds_never_used_rows(shape, tokens, entry):
-    """A slot map that the caller seeded, full but for a few slots, a tenth of
-    its rows never used (last_used -1)."""
+def test_delta_lds_never_used_rows(shape, never, tokens, entry):
+    """A slot map that the caller seeded, full but for a few slots, a tenth or
+    all of its rows never used (last_used -1): those leave first, by id."""
     L, F, k, C = shape
-    say(f"[delta lds never used] {shape} {tokens} {entry}")
+    say(f"[delta lds never used] {shape} {never} {tokens} {entry}")
     rng = np.random.default_rng(C + tokens)
-    pair = Pair(shape, *seeded(rng, shape, C - 7, C // 10, tokens))
+    P, Q, U = seeded(rng, shape, C - 7, int(never * (C - 7)), tokens)
+    pair = Pair(shape, P, Q, U)
+    st = orc.State(L, F, C)
+    st.slot_of[:], st.neuron_of[:], st.last_used[:] = P, Q, U
     for i in range(3):
         ids = np.stack([np.sort(rng.choice(F, k, replace=False)) for _ in range(L)]).astype(np.int32)
         got, err = pair.step(entry, tokens + i, ids)
         assert err == 0
-        assert np.all(got["counts"][:, 2] > 0)  # victims
+        ref = orc.delta(tokens + i, ids, st, C)
+        assert np.all(ref["counts"][:, 2] > 0)  # victims
+        compare_delta(got, ref, L)
+        check_state(pair.lds, st)
