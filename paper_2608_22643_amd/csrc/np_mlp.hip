@@ -40,6 +40,7 @@
 #include <map>
 #include <mutex>
 #include <tuple>
+#include <type_traits>
 
 #include "np_device.hpp"
 
@@ -230,150 +231,169 @@ __global__ __launch_bounds__(MAXT) void sparse_mlp_rows_kernel(MlpArgs a) {
     gen0 = __hip_atomic_load((int*)((char*)a.ws + WS_BAR_GEN), __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
 
-  // The first round's slots (lane r: row r of the team) come straight from
-  // the list; the whole range goes to LDS behind them, so that the rounds
-  // read their slots without a memory access queued behind the records.  -1:
-  // past the range, or a row without a resident slot, which is reported.
-  const bool in0 = lane < R && row_begin + team * R + lane < row_end;
-  const int raw0 = in0 ? row_slot(a, row_begin + team * R + lane, b) : -1;
-  const int nrows = row_end - row_begin;
-  const bool fill = !dense && (int)threadIdx.x < nrows;
-  auto checked = [&](int slot) {
-    if (slot >= 0 && slot < a.C) return slot;
-    raise_error(a.ws, NP_DEVERR_NOT_RESIDENT);
-    return -1;
-  };
-  const int rawf = fill ? row_slot(a, row_begin + threadIdx.x, b) : 0;
-  // Record loads are buffer loads with no branches around them: lanes past
-  // the column slice and rows without a slot use an out-of-range offset and
-  // read zeros without touching memory.
-  const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(a.res_layer, a.layer_bytes);
-  const uint32_t third = (uint32_t)a.NV * 16u;
-  auto row_off = [&](int slots, int r) {
-    const int slot = __builtin_amdgcn_readlane(slots, r);
-    return slot >= 0 ? (uint32_t)slot * 3u * third : BUF_OOB;
-  };
-  int cur = raw0 >= 0 && raw0 < a.C ? raw0 : -1;
-  uint4 xr[CPL];
-  bool vok[CPL];
   uint32_t loff[CPL];  // this lane's byte offset within a third of a record
+  bool vok[CPL];
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
     const int v = v0 + lane + WAVE * c;
     vok[c] = v < a.NV;
     loff[c] = vok[c] ? (uint32_t)v * 16u : BUF_OOB;
-    xr[c] = a.x[vok[c] ? v : 0];
   }
-  __builtin_amdgcn_sched_barrier(0);
-  // the first round's records (offsets: both terms < 2^31, no wrap)
-  u32x4_t gw[R][CPL], uw[R][CPL], dw[R][CPL];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const uint32_t roff = row_off(cur, r);
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      gw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], 0);
-      uw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], third);
-    }
-  }
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const uint32_t roff = row_off(cur, r);
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) dw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], 2 * third);
-  }
-  if (!dense) {
-    if (fill) slot_s[threadIdx.x] = checked(rawf);
-    for (int i = threadIdx.x + blockDim.x; i < nrows; i += blockDim.x)
-      slot_s[i] = checked(row_slot(a, row_begin + i, b));
-    lds_barrier();
-  }
-  auto round_slots = [&](int rb) {
-    const int row = rb + team * R + lane;
-    if (lane >= R || row >= row_end) return -1;
-    return dense ? row_slot(a, row, b) : slot_s[row - row_begin];
-  };
-  int nxt = round_slots(row_begin + teams * R);
   float yacc[CPL][V];
 #pragma unroll
   for (int c = 0; c < CPL; ++c)
 #pragma unroll
     for (int e = 0; e < V; ++e) yacc[c][e] = 0.f;
 
-  // every wave runs the same number of rounds (a barrier inside)
-  int par = 0;
-  for (int rb = row_begin; rb < row_end; rb += teams * R, par ^= 1) {
-    const int nxt2 = round_slots(rb + 2 * teams * R);  // the round after the next
-    float v[NVAL];
+  if (row_begin < row_end) {  // the whole workgroup
+    // The first round's slots (lane r: row r of the team) come straight from
+    // the list; the whole range goes to LDS behind them, so that the rounds
+    // read their slots without a memory access queued behind the records.  -1:
+    // past the range, or a row without a resident slot, which is reported.
+    const bool in0 = lane < R && row_begin + team * R + lane < row_end;
+    const int raw0 = in0 ? row_slot(a, row_begin + team * R + lane, b) : -1;
+    const int nrows = row_end - row_begin;
+    const bool fill = !dense && (int)threadIdx.x < nrows;
+    auto checked = [&](int slot) {
+      if (slot >= 0 && slot < a.C) return slot;
+      raise_error(a.ws, NP_DEVERR_NOT_RESIDENT);
+      return -1;
+    };
+    const int rawf = fill ? row_slot(a, row_begin + threadIdx.x, b) : 0;
+    // Record loads are buffer loads with no branches around them: lanes past
+    // the column slice and rows without a slot use an out-of-range offset and
+    // read zeros without touching memory.
+    const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(a.res_layer, a.layer_bytes);
+    const uint32_t third = (uint32_t)a.NV * 16u;
+    auto row_off = [&](int slots, int r) {
+      const int slot = __builtin_amdgcn_readlane(slots, r);
+      return slot >= 0 ? (uint32_t)slot * 3u * third : BUF_OOB;
+    };
+    int cur = raw0 >= 0 && raw0 < a.C ? raw0 : -1;
+    uint4 xr[CPL];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) xr[c] = a.x[vok[c] ? v0 + lane + WAVE * c : 0];
+    __builtin_amdgcn_sched_barrier(0);
+    // the first round's records (offsets: both terms < 2^31, no wrap)
+    u32x4_t gw[R][CPL], uw[R][CPL], dw[R][CPL];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      float g = 0.f, u = 0.f;
-      const uint32_t roff = row_off(nxt, r);
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) {  // lanes past the slice hold zeros
-        g = T::dot(as_uint4(gw[r][c]), xr[c], g);
-        u = T::dot(as_uint4(uw[r][c]), xr[c], u);
-      }
-      // the refill stays behind the last use of its registers (moved ahead
-      // of it, it would take registers of its own and a copy at the end of
-      // the round that waits for every load): the empty statement uses the
-      // sums, and neither it nor a load moves over the scheduling barrier
-      asm volatile("" : "+v"(g), "+v"(u));
-      __builtin_amdgcn_sched_barrier(0);
+      const uint32_t roff = row_off(cur, r);
 #pragma unroll
       for (int c = 0; c < CPL; ++c) {
         gw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], 0);
         uw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], third);
       }
-      v[r] = g;
-      v[R + r] = u;
     }
     __builtin_amdgcn_sched_barrier(0);
-    wave_reduce_scatter<NVAL>(v);  // lane l holds the wave sum of value l / G
-    float t = v[0];
-    if (P > 1) {
-      // the P waves' sums of each value meet in LDS: lane NVAL*q + i reads
-      // value i of waves q, q + G, ..., and a fixed tree over the lanes of
-      // a value adds them
-      if (lane % G == 0) gu[par][wid][lane / G] = t;
-      lds_barrier();
-      const int val = lane % NVAL;
-      t = 0.f;
-      for (int q = lane / NVAL; q < P; q += G) t += gu[par][team * P + q][val];
-      if constexpr (NVAL <= 4) t += dpp_xor4(t);
-      if constexpr (NVAL <= 8) t += dpp_f32<DPP_XOR8>(t);
-      t = swap16_add(t, t);
-      t = swap32_add(t, t);
-    }
-    float act[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      // value i sits in lane i after the exchange, in lanes i*G.. without it
-      const int lg = P > 1 ? r : r * G, lu = P > 1 ? R + r : (R + r) * G;
-      const float gs = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), lg));
-      const float us = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), lu));
-      act[r] = gated(a.act, gs, us);
-      // a row without a slot adds nothing, whatever x holds
-      if (fabsf(act[r]) < thr || __builtin_amdgcn_readlane(cur, r) < 0) act[r] = 0.f;
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const uint32_t roff = row_off(nxt, r);
-#pragma unroll
-      for (int c = 0; c < CPL; ++c)  // lanes past the slice accumulate values never written
-        T::axpy(yacc[c], act[r], as_uint4(dw[r][c]));
-#pragma unroll
-      for (int c = 0; c < CPL; ++c)
-#pragma unroll
-        for (int e = 0; e < V; ++e) asm volatile("" : "+v"(yacc[c][e]));
-      __builtin_amdgcn_sched_barrier(0);
+      const uint32_t roff = row_off(cur, r);
 #pragma unroll
       for (int c = 0; c < CPL; ++c) dw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], 2 * third);
     }
-    __builtin_amdgcn_sched_barrier(0);
-    cur = nxt;
-    nxt = nxt2;
+    if (!dense) {
+      if (fill) slot_s[threadIdx.x] = checked(rawf);
+      for (int i = threadIdx.x + blockDim.x; i < nrows; i += blockDim.x)
+        slot_s[i] = checked(row_slot(a, row_begin + i, b));
+      lds_barrier();
+    }
+    const int step = teams * R;
+    auto round_slots = [&](int rb) {
+      const int row = rb + team * R + lane;
+      if (lane >= R || row >= row_end) return -1;
+      return dense ? row_slot(a, row, b) : slot_s[row - row_begin];
+    };
+    int nxt = round_slots(row_begin + step);
+    int par = 0;
+    auto round = [&](auto refill) {
+      constexpr bool REFILL = decltype(refill)::value;
+      float v[NVAL];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        float g = 0.f, u = 0.f;
+        const uint32_t roff = REFILL ? row_off(nxt, r) : 0u;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {  // lanes past the slice hold zeros
+          g = T::dot(as_uint4(gw[r][c]), xr[c], g);
+          u = T::dot(as_uint4(uw[r][c]), xr[c], u);
+        }
+        // the refill stays behind the last use of its registers (moved ahead
+        // of it, it would take registers of its own and a copy at the end of
+        // the round that waits for every load): the empty statement uses the
+        // sums, and neither it nor a load moves over the scheduling barrier
+        asm volatile("" : "+v"(g), "+v"(u));
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (REFILL) {
+#pragma unroll
+          for (int c = 0; c < CPL; ++c) {
+            gw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], 0);
+            uw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], third);
+          }
+        }
+        v[r] = g;
+        v[R + r] = u;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      wave_reduce_scatter<NVAL>(v);  // lane l holds the wave sum of value l / G
+      float t = v[0];
+      if (P > 1) {
+        // the P waves' sums of each value meet in LDS: lane NVAL*q + i reads
+        // value i of waves q, q + G, ..., and a fixed tree over the lanes of
+        // a value adds them
+        if (lane % G == 0) gu[par][wid][lane / G] = t;
+        lds_barrier();
+        const int val = lane % NVAL;
+        t = 0.f;
+        for (int q = lane / NVAL; q < P; q += G) t += gu[par][team * P + q][val];
+        if constexpr (NVAL <= 4) t += dpp_xor4(t);
+        if constexpr (NVAL <= 8) t += dpp_f32<DPP_XOR8>(t);
+        t = swap16_add(t, t);
+        t = swap32_add(t, t);
+      }
+      float act[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        // value i sits in lane i after the exchange, in lanes i*G.. without it
+        const int lg = P > 1 ? r : r * G, lu = P > 1 ? R + r : (R + r) * G;
+        const float gs = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), lg));
+        const float us = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), lu));
+        act[r] = gated(a.act, gs, us);
+        // a row without a slot adds nothing, whatever x holds
+        if (fabsf(act[r]) < thr || __builtin_amdgcn_readlane(cur, r) < 0) act[r] = 0.f;
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint32_t roff = REFILL ? row_off(nxt, r) : 0u;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)  // lanes past the slice accumulate values never written
+          T::axpy(yacc[c], act[r], as_uint4(dw[r][c]));
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)
+#pragma unroll
+          for (int e = 0; e < V; ++e) asm volatile("" : "+v"(yacc[c][e]));
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (REFILL) {
+#pragma unroll
+          for (int c = 0; c < CPL; ++c)
+            dw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], 2 * third);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // every wave runs the same number of rounds (a barrier inside); the last
+    // is a copy of its own that refills nothing: out-of-range loads reach no
+    // memory, but each holds the load path for 16 cycles (us per call with
+    // them and without, d 8192 f16: 16 rows 8.47, 7.55; 2867 rows 29.5, 28.9;
+    // d 4096 f16, 1651 rows 12.3, 12.0)
+    int rb = row_begin;
+    for (; rb + step < row_end; rb += step, par ^= 1) {
+      const int nxt2 = round_slots(rb + 2 * step);  // the round after the next
+      round(std::true_type());
+      cur = nxt;
+      nxt = nxt2;
+    }
+    round(std::false_type());
   }
   // teams 1.. hand their partial y to team 0 through LDS (fixed order)
   if (teams > 1) {
