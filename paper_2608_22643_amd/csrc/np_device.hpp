@@ -296,6 +296,28 @@ __device__ inline float sum_quads(float v) {
   return swap32_add(v, v);
 }
 
+// The same in fp64.
+template <int CTRL>
+__device__ inline double dpp_f64(double v) {
+  const int2 u = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(u.x, CTRL, 0xF, 0xF, true),
+                                              __builtin_amdgcn_mov_dpp(u.y, CTRL, 0xF, 0xF, true)));
+}
+__device__ inline double sum_quads(double v) {
+  v += dpp_f64<DPP_XOR3>(dpp_f64<DPP_XOR7>(v));
+  v += dpp_f64<DPP_XOR8>(v);
+  uint2 u = __builtin_bit_cast(uint2, v);
+  auto lo = __builtin_amdgcn_permlane16_swap(u.x, u.x, false, false);
+  auto hi = __builtin_amdgcn_permlane16_swap(u.y, u.y, false, false);
+  v = __builtin_bit_cast(double, make_uint2(lo[0], hi[0])) +
+      __builtin_bit_cast(double, make_uint2(lo[1], hi[1]));
+  u = __builtin_bit_cast(uint2, v);
+  lo = __builtin_amdgcn_permlane32_swap(u.x, u.x, false, false);
+  hi = __builtin_amdgcn_permlane32_swap(u.y, u.y, false, false);
+  return __builtin_bit_cast(double, make_uint2(lo[0], hi[0])) +
+         __builtin_bit_cast(double, make_uint2(lo[1], hi[1]));
+}
+
 // Reduce-scatter of N values (N = 4, 8 or 16) over a wave: on entry every
 // lane holds v[0..N-1]; on return lane l holds in v[0] the wave sum of value
 // l / (64/N) (every lane of that group of 64/N lanes holds it).  Each halving

@@ -199,6 +199,9 @@ __global__ __launch_bounds__(MAXT) void sparse_mlp_rows_kernel(MlpArgs a) {
   constexpr int NVAL = 2 * R;           // g and u of each row of a round
   constexpr int G = WAVE / NVAL;        // lanes holding one reduced value
   constexpr int MAXW = MAXT / WAVE;     // waves of a workgroup
+  // fp32: a round's rows are summed before they join y, so that y is a chain
+  // of rounds and not of rows (16-bit results round such differences away)
+  constexpr bool ROUND_SUM = T::dtype == NP_F32;
   // round parity (a wave may write the next round's sums while another still
   // reads this round's), wave, value
   __shared__ float gu[2][MAXW][NVAL];
@@ -362,22 +365,29 @@ __global__ __launch_bounds__(MAXT) void sparse_mlp_rows_kernel(MlpArgs a) {
         // a row without a slot adds nothing, whatever x holds
         if (fabsf(act[r]) < thr || __builtin_amdgcn_readlane(cur, r) < 0) act[r] = 0.f;
       }
+      float rsum[CPL][V] = {};  // ROUND_SUM
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const uint32_t roff = REFILL ? row_off(nxt, r) : 0u;
 #pragma unroll
         for (int c = 0; c < CPL; ++c)  // lanes past the slice accumulate values never written
-          T::axpy(yacc[c], act[r], as_uint4(dw[r][c]));
+          T::axpy(ROUND_SUM ? rsum[c] : yacc[c], act[r], as_uint4(dw[r][c]));
 #pragma unroll
         for (int c = 0; c < CPL; ++c)
 #pragma unroll
-          for (int e = 0; e < V; ++e) asm volatile("" : "+v"(yacc[c][e]));
+          for (int e = 0; e < V; ++e) asm volatile("" : "+v"((ROUND_SUM ? rsum : yacc)[c][e]));
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (REFILL) {
 #pragma unroll
           for (int c = 0; c < CPL; ++c)
             dw[r][c] = buf_load16v_nt(rsrc, roff + loff[c], 2 * third);
         }
+      }
+      if constexpr (ROUND_SUM) {
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)
+#pragma unroll
+          for (int e = 0; e < V; ++e) yacc[c][e] += rsum[c][e];
       }
       __builtin_amdgcn_sched_barrier(0);
     };
@@ -474,50 +484,58 @@ __global__ __launch_bounds__(MAXT) void sparse_mlp_rows_kernel(MlpArgs a) {
 // fp32, so the block of 256 threads that owns 16 columns reads n_wg * 64
 // contiguous bytes; the per-thread sums meet through a shuffle tree within
 // each wave and then in wave order through LDS.
+// In fp32 the partials meet in fp64: short rounds leave many partials for few
+// rows, whose sums would add more rounding than the rows themselves (rel.
+// error of y, d 512, 51 to 1000 rows: 1.35-1.53e-7 summed in fp32, 1.23-1.37e-7
+// in fp64, for 0.05 to 0.1 us a call).
 constexpr int RED_COLS = 16;
 
 template <class T>
 __global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict__ partials,
                                                          int n_wg, int d, void* y) {
+  using A = std::conditional_t<T::dtype == NP_F32, double, float>;
   // thread t reads 16-byte piece q = t % 4 of partial rows t / 4, t / 4 + 64,
   // ...: each wave instruction reads 1 KiB of contiguous memory
-  __shared__ float4 red[4][4];  // wave, piece
+  __shared__ A red[4][RED_COLS];  // wave, column
   const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE, q = t & 3, rs = t >> 2;
   const int col = blockIdx.x * RED_COLS + 4 * q;
   const bool cok = col < d;
-  const float* blk = partials + (size_t)blockIdx.x * n_wg * RED_COLS + 4 * q;
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int r0 = rs; r0 < n_wg; r0 += 256) {  // rows in a fixed order
-    float4 v[4];
+  // rows past n_wg read out of range: zeros; columns past d are not stored
+  const __amdgpu_buffer_rsrc_t blk =
+      make_rsrc(partials + (size_t)blockIdx.x * n_wg * RED_COLS, (uint32_t)n_wg * RED_COLS * 4u);
+  A acc[4] = {};
+  auto add = [&](int r0, auto count) {  // rows r0, r0 + 64, ..., all loads first
+    constexpr int N = decltype(count)::value;
+    u32x4_t v[N];
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const int row = r0 + 64 * h;
-      v[h] = (row < n_wg && cok) ? *(const float4*)(blk + (size_t)row * RED_COLS)
-                                 : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+    for (int h = 0; h < N; ++h)
+      v[h] = buf_load16v(blk, ((uint32_t)(r0 + 64 * h) * RED_COLS + 4u * q) * 4u, 0);
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      acc.x += v[h].x;
-      acc.y += v[h].y;
-      acc.z += v[h].z;
-      acc.w += v[h].w;
-    }
+    for (int h = 0; h < N; ++h)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += __uint_as_float(v[h][e]);
+  };
+  if (n_wg <= 64) add(rs, std::integral_constant<int, 1>());
+  else
+    for (int r0 = 0; r0 < n_wg; r0 += 256) add(r0 + rs, std::integral_constant<int, 4>());
+  // the wave's 16 row groups of each piece: a fixed tree over lane bits 2..5,
+  // leaving lane q with piece q's wave sum
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    acc[e] = sum_quads(acc[e]);
+    if (lane < 4) red[w][4 * lane + e] = acc[e];
   }
-  // the wave's 16 row groups of each piece: a fixed shuffle tree over lane
-  // bits 2..5, leaving lane q with piece q's wave sum
-  acc = make_float4(sum_quads(acc.x), sum_quads(acc.y), sum_quads(acc.z), sum_quads(acc.w));
-  if (lane < 4) red[w][lane] = acc;
   __syncthreads();
   if (t < 4 && cok) {  // waves in order
-    float4 o = red[0][t];
+    float o[4];
 #pragma unroll
-    for (int k = 1; k < 4; ++k) {
-      o.x += red[k][t].x;
-      o.y += red[k][t].y;
-      o.z += red[k][t].z;
-      o.w += red[k][t].w;
+    for (int e = 0; e < 4; ++e) {
+      A v = red[0][4 * t + e];
+#pragma unroll
+      for (int k = 1; k < 4; ++k) v += red[k][4 * t + e];
+      o[e] = (float)v;
     }
-    store_y4<T>(y, col, o);
+    store_y4<T>(y, col, make_float4(o[0], o[1], o[2], o[3]));
   }
 }
 

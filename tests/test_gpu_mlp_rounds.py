@@ -72,3 +72,55 @@ def test_mlp_rounds_exact(d, dt, rows, wg, monkeypatch):
     torch.cuda.synchronize()
     assert np.all(decode_y(orc, dt, y.cpu().numpy()) == 0)
     assert B.np_device_error(bufs.ws) == B.NP_DEVERR_NOT_RESIDENT
+
+
+def chains_of_256(a, down):
+    """sum_j a[j] down[j] in fp32 as 256 workgroups sum it row by row (one fused
+    multiply-add a row), their sums met in the reduce kernel's order."""
+    f32, F = np.float32, len(a)
+    parts = np.zeros((256, down.shape[1]), f32)
+    for j in range(F):  # workgroup b takes rows b, b + 256, ...; a[j] has 8 bits: the product is exact
+        p = parts[j % 256]
+        p[:] = (p.astype(np.float64) + np.float64(a[j]) * down[j]).astype(f32)
+    v = parts.reshape(4, 4, 16, -1)  # row 64 h + 16 w + q: thread order within a column block
+    acc = v[0].copy()
+    for h in range(1, 4):
+        acc += v[h]
+    for bit in (1, 2, 4, 8):
+        acc = acc + acc[:, np.arange(16) ^ bit]
+    y = acc[0, 0].copy()
+    for w in range(1, 4):
+        y = y + acc[w, 0]
+    return y.astype(np.float64)
+
+
+@pytest.mark.parametrize("dense", [True, False], ids=["dense", "sparse"])
+def test_mlp_fp32_sums_no_worse_than_256_chains(dense):
+    """In fp32 the down projection of a long range is no further from the exact
+    sum than 256 plain chains of rows would be, although fewer workgroups run:
+    every g is 1 and every u has 8 bits, so the activations are exact and the
+    sum's rounding is all there is.  6000 rows run on 188 workgroups of 32; the
+    chains of 24 that 256 workgroups have are 1.16e-7 off, chains of 32 rows
+    1.28e-7 (dense), sums by rounds of 4 that meet in fp64 0.75e-7."""
+    d, F = 1024, 6000
+    say(f"[mlp fp32 sums] dense {dense}")
+    rng = np.random.default_rng(3)
+    a = (rng.integers(1, 256, F) * rng.choice([-1, 1], F)).astype(np.float32) / 64
+    rec = np.zeros((F, 3 * d), np.float32)
+    rec[:, 0], rec[:, d] = 1.0, a
+    rec[:, 2 * d:] = rng.standard_normal((F, d)).astype(np.float32)
+    exact = a.astype(np.float64) @ rec[:, 2 * d:].astype(np.float64)
+    x = torch.zeros(d, device=DEV)
+    x[0] = 1.0
+    y = torch.zeros(d, device=DEV)
+    shape = B.make_shape(1, d, F, 8, F, F, "f32")
+    ws = torch.zeros(B.np_workspace_size(shape), dtype=torch.uint8, device=DEV)
+    res = torch.from_numpy(rec).to(DEV)
+    if dense:
+        B.np_dense_mlp(shape, res, x, y, ws)
+    else:
+        B.np_sparse_mlp(shape, 0, x, res, torch.arange(F, dtype=torch.int32, device=DEV), F, y, ws)
+    torch.cuda.synchronize()
+    err = np.linalg.norm(y.cpu().numpy() - exact)
+    assert err <= np.linalg.norm(chains_of_256(a, rec[:, 2 * d:]) - exact)
+    assert B.np_device_error(ws) == 0
