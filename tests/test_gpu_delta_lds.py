@@ -237,3 +237,55 @@ def test_delta_lds_never_used_rows(shape, never, tokens, entry):
         assert np.all(ref["counts"][:, 2] > 0)  # victims
         compare_delta(got, ref, L)
         check_state(pair.lds, st)
+
+
+@pytest.mark.parametrize("entry", ["delta", "delta_n", "select_delta"])
+@pytest.mark.parametrize("kind", ["stale_slot", "slot_range", "lost_slot", "two_slots", "neuron_range"])
+@pytest.mark.parametrize("shape", [(2, 3000, 300, 900), (2, 11008, 1651, 5504),
+                                   (1, 28672, 2867, 8601)], ids=lambda s: f"F{s[1]}")
+def test_delta_lds_inconsistent_state(shape, kind, entry):
+    """A slot map with a twentieth of its entries wrong, in a full buffer: the
+    LDS kernels' checked path gives every list, every state entry and the error
+    word that the kernel of its own for larger layers gives."""
+    L, F, k, C = shape
+    say(f"[delta lds inconsistent] {shape} {kind} {entry}")
+    rng = np.random.default_rng(C)
+    P, Q, U = seeded(rng, shape, C - 7, 5, 50)
+    for l in range(L):
+        held = rng.choice(np.flatnonzero(P[l] >= 0), C // 20, replace=False)
+        free = rng.choice(np.flatnonzero(P[l] < 0), C // 20, replace=False)
+        if kind == "stale_slot":  # a neuron names a slot that another holds
+            P[l, free] = P[l, held]
+        elif kind == "slot_range":
+            P[l, free] = C + 4 + np.arange(len(free))
+            P[l, held[::2]] = -3
+        elif kind == "lost_slot":  # a slot names a neuron that does not know
+            P[l, held] = -1
+        elif kind == "two_slots":  # two slots name the same neuron
+            Q[l, P[l, held[::2]]] = held[1::2][:len(held[::2])][0]
+        else:
+            Q[l, P[l, held[::2]]] = F + 3
+            Q[l, P[l, held[1::2]]] = -5
+    pair = Pair(shape, P, Q, U)
+    for i in range(3):
+        ids = np.stack([np.sort(rng.choice(F, k, replace=False)) for _ in range(L)]).astype(np.int32)
+        got, err = pair.step(entry, 50 + i, ids)
+        assert np.all(got["counts"][:, 2] > 0)
+        if i == 0:
+            assert err == B.NP_DEVERR_STATE
+
+
+@pytest.mark.parametrize("shape", [(2, 3000, 300, 900), (2, 11008, 1651, 5504)], ids=lambda s: f"F{s[1]}")
+def test_delta_lds_bad_counts_and_order(shape):
+    """Counts outside [0, k] and ids in descending order, against the kernel
+    for larger layers."""
+    L, F, k, C = shape
+    say(f"[delta lds counts and order] {shape}")
+    rng = np.random.default_rng(C)
+    pair = Pair(shape, *seeded(rng, shape, C - 7, 5, 50))
+    for i, counts in enumerate((None, [k + 3, k], [-2, k // 2])):
+        ids = np.stack([np.sort(rng.choice(F, k, replace=False)) for _ in range(L)]).astype(np.int32)
+        _, err = pair.step("delta_n", 50 + i, ids, counts)
+        assert (err != 0) == (i > 0)
+    ids = np.stack([np.sort(rng.choice(F, k, replace=False))[::-1] for _ in range(L)]).astype(np.int32)
+    pair.step("delta", 60, np.ascontiguousarray(ids))
