@@ -34,7 +34,7 @@ SHAPES = {
     "d1024_bf16": cfg_small("d1024_bf16", 3, 1024, 5000, 16, 512, 1200, "bf16"),
     "d2048_f16": cfg_small("d2048_f16", 2, 2048, 7000, 16, 1000, 2000, "f16"),
     "d4096_bf16": cfg_small("d4096_bf16", 2, 4096, 11008, 16, 1651, 5504, "bf16"),
-    # 9 and 10 waves per workgroup: 8-row rounds in four stages
+    # 9 and 10 waves per workgroup
     "d4608_bf16": cfg_small("d4608_bf16", 2, 4608, 5000, 16, 1200, 2000, "bf16"),
     "d5120_f16": cfg_small("d5120_f16", 2, 5120, 6000, 16, 1658, 2600, "f16"),
     # 128-vector slices: 8 waves of two vectors per lane, 4-row rounds
@@ -42,9 +42,8 @@ SHAPES = {
 }
 PATHS = {"colsplit": {"NP_MLP_COLSPLIT": "1"}, "two_kernel": {},
          "fused": {"NP_MLP_FUSED": "1"}}
-# further launch rules at the 7B width, checked with dyadic records: two
-# rounds of 8 rows (k above 8 x 256), and a small set in 4-row rounds on
-# twice the workgroups (fewer than 128 workgroups of 8 rows)
+# more row counts at the 7B width, checked with dyadic records: four 4-row
+# rounds on 207 workgroups, and one round on 138
 DYADIC_SHAPES = {**SHAPES,
                  "d4096_f16_k3302": cfg_small("d4096_f16_k3302", 1, 4096, 6000, 16, 3302, 4000,
                                               "f16"),
@@ -104,9 +103,9 @@ def test_mlp_paths_dyadic_bit_exact(name, path, monkeypatch):
     multiples of 2^-6, a of 2^-12 below 2^12 and every partial sum of y a
     multiple of 2^-18 below 2^6, so every sum is exact in fp32 in any order
     and y is the exact value rounded once to nearest even -- on every launch
-    shape of the rows kernel (4 to 10 waves of one-vector slices, 8 waves of
-    two-vector slices in 4-row rounds, two rounds of 8 rows, a small set in
-    4-row rounds), every reduction path and every row
+    shape of the rows kernel here (1 to 10 waves of one-vector slices, 8 waves
+    of two-vector slices, one round of 4 rows to four, 2-row rounds for the
+    row counts below 512), every reduction path and every row
     count, the GPU's y equals the oracle's value for value (the sign of a
     zero aside)."""
     for k_, v_ in PATHS[path].items():
@@ -224,7 +223,7 @@ def test_mlp_paths_bad_slot(path, monkeypatch):
 
 
 def test_mlp_multi_round():
-    """More active rows than one 8-row round per workgroup (2 to 3 rounds,
+    """More active rows than one round per workgroup (2 to 5 rounds of 4 rows,
     workgroups with different round counts in one launch), and SwiGLU with a
     threshold on a second layer."""
     cfg = cfg_small("d4096_many", 2, 4096, 6000, 16, 4200, 4500, "f16")

@@ -5,10 +5,12 @@ set) -- against the two separate calls and against the oracle's O2 and O3.
 Bar: bit for bit.  The mask, the active ids, the three state arrays, every
 defined entry of the delta lists and the error word must equal those of the
 two calls on the same inputs, and the ids and the delta must equal the
-oracle's, run on the same fp32 scores.  Shapes cover the fused kernel (F up
-to 16384, C up to 8192, k up to 4096: the 7B and 13B layer shapes, the edge
-of each limit, F not a multiple of 4 or of 32, C not a multiple of 32) and
-the shapes that fall back to the two kernels (F above the limit, k above it).
+oracle's, run on the same fp32 scores.  Shapes cover the fused kernel's builds
+(the 7B and 13B layer shapes, F up to and past 16384, k up to and past 4096, F
+not a multiple of 4 or of 32, C not a multiple of 32); test_gpu_delta_lds.py
+covers its limits and the shapes past them, and compares its path for
+inconsistent slot maps, which np_delta shares, with the kernel for larger
+layers.
 Scores follow an AR(1) sequence across tokens, so consecutive active sets
 overlap and the resident buffer fills, evicts and reuses slots; some tokens
 quantise the scores to a few levels so that the k-th score is tied many
@@ -41,8 +43,8 @@ SHAPES = {
     "7b_layers": cfg_small("7b_layers", 4, 64, 11008, 1651, 5504),
     "13b_layers": cfg_small("13b_layers", 3, 64, 13824, 1658, 5529),  # C % 32 != 0
     "fused_max": cfg_small("fused_max", 2, 64, 16384, 4096, 8192),
-    "f_over": cfg_small("f_over", 2, 64, 16385, 2000, 6000),   # two kernels
-    "k_over": cfg_small("k_over", 2, 64, 14336, 4097, 8192),   # two kernels
+    "f_over": cfg_small("f_over", 2, 64, 16385, 2000, 6000),   # 32 ids a thread
+    "k_over": cfg_small("k_over", 2, 64, 14336, 4097, 8192),   # 8 actives a thread
 }
 
 
