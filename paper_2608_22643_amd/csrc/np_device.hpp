@@ -380,9 +380,6 @@ __device__ inline uint32_t wave_incl_scan(uint32_t v) {
   v += dpp_or_zero<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
   return v;
 }
-__device__ inline uint32_t wave_total(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), WAVE - 1);
-}
 __device__ inline uint32_t wave_max(uint32_t v) {
   auto step = [&](uint32_t o) { v = o > v ? o : v; };
   step(dpp_or_zero<0x111, 0xF>(v));
@@ -412,23 +409,6 @@ __device__ inline uint32_t block_excl_scan_once(uint32_t v, uint32_t* lds, uint3
       w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)t, w > 0 ? w - 1 : 0) : 0u;
   *total = (uint32_t)__builtin_amdgcn_readlane((int)t, NW - 1);
   return before + incl - v;
-}
-
-// Exclusive prefix over the waves of a value that is the same in every lane
-// of a wave (at most 16 waves); barrier and lds as above.
-__device__ inline uint32_t wave_prefix_once(uint32_t v, uint32_t* lds, int nw, uint32_t* total) {
-  const int lane = threadIdx.x & (WAVE - 1);
-  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
-  if (lane == 0) lds[w] = v;
-  lds_barrier();
-  const uint32_t t = row_incl_scan(lane < nw ? lds[lane] : 0u);
-  *total = (uint32_t)__builtin_amdgcn_readlane((int)t, nw - 1);
-  return w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)t, w > 0 ? w - 1 : 0) : 0u;
-}
-
-// Set bits of m below this lane.
-__device__ inline uint32_t lanes_below(uint64_t m) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 // The same with lds free for reuse on return (a second barrier).

@@ -108,9 +108,6 @@ __device__ inline void store_y1(void* y, int col, float v) {
   else ((uint16_t*)y)[col] = (uint16_t)T::from_f32(v);
 }
 
-// Grid barrier, then the column reduction of this workgroup's chunks.  Every
-// thread of the workgroup calls it; thread 0 holds `gen0`, the generation
-// read at entry.  red: blockDim.x float4 of LDS.
 // Grid barrier over the n_wg workgroups of the launch: every thread calls
 // it after its agent-scope stores; thread 0 holds `gen0`, the generation
 // read at entry.  The last workgroup to arrive resets the arrival counter and
@@ -138,6 +135,9 @@ __device__ inline void grid_barrier(void* ws, int n_wg, int gen0) {
   __syncthreads();
 }
 
+// Grid barrier, then the column reduction of this workgroup's blocks.  Every
+// thread of the workgroup calls it; thread 0 holds `gen0`.  red: blockDim.x
+// float4 of LDS.
 template <class T>
 __device__ inline void fused_reduce(const MlpArgs& a, int gen0, float4* red) {
   grid_barrier(a.ws, a.n_wg, gen0);
@@ -196,6 +196,7 @@ __device__ inline void fused_reduce(const MlpArgs& a, int gen0, float4* red) {
 template <class T, int CPL, int R, int MAXT, bool FUSED>
 __global__ __launch_bounds__(MAXT) void sparse_mlp_rows_kernel(MlpArgs a) {
   constexpr int V = T::V;
+  static_assert(R == 2 || R == 4, "the exchange below");
   constexpr int NVAL = 2 * R;           // g and u of each row of a round
   constexpr int G = WAVE / NVAL;        // lanes holding one reduced value
   constexpr int MAXW = MAXT / WAVE;     // waves of a workgroup
@@ -350,7 +351,7 @@ __global__ __launch_bounds__(MAXT) void sparse_mlp_rows_kernel(MlpArgs a) {
         t = 0.f;
         for (int q = lane / NVAL; q < P; q += G) t += gu[par][team * P + q][val];
         if constexpr (NVAL <= 4) t += dpp_xor4(t);
-        if constexpr (NVAL <= 8) t += dpp_f32<DPP_XOR8>(t);
+        t += dpp_f32<DPP_XOR8>(t);
         t = swap16_add(t, t);
         t = swap32_add(t, t);
       }
@@ -775,15 +776,13 @@ static hipError_t mlp_t(const np_shape& s, int layer, const void* x, const void*
   // take 26.2 us for the rows, 16 waves of 64 vectors 26.5)
   const int cpl = (a.NV + WAVE - 1) / WAVE <= 10 ? 1 : 2;
   a.P = (a.NV + WAVE * cpl - 1) / (WAVE * cpl);
-  // rows per team and round: 4 (with the registers refilled as they are
-  // used, more rows in flight gain nothing: 7B, k = 1651, 9.8 us for the
-  // rows with 4, 10.1 with 8), 2 for 128-vector slices over more than 8
-  // waves (128 registers per lane)
-  // Fewer than 512 rows: 2 a round on twice the workgroups (d 256, n = 400:
-  // 5.4 against 5.7 us per call)
+  // rows per team and round: 4 (more rows in flight gain nothing once the
+  // registers are refilled as they are used: 7B, k = 1651, 8 rows a round took
+  // 10.1 us for the rows, 4 take 9.8), 2 for 128-vector slices over more than
+  // 8 waves (128 registers per lane).  Fewer than 512 rows: 2 a round on twice
+  // the workgroups (d 256, n = 400: 5.4 against 5.7 us per call)
   int R = cpl == 1 ? env_int("NP_MLP_R", n_active < 512 ? 2 : 4) : (a.P <= 8 ? 4 : 2);
-  if (R != 2 && R != 8) R = cpl == 1 ? 4 : R;
-  if (R == 8 && a.P > 8) R = 4;
+  if (R != 2) R = 4;
   // narrow rows: up to 4 waves in row teams, while 128 workgroups would have
   // a full round (us per call with 1, 2 and 4 teams: d 256 f16, P = 1, n =
   // 5000: 9.2, 7.9, 7.4; d 512 f16, P = 1, 8000 dense rows: 11.7, 9.1, 9.0; d
@@ -798,11 +797,17 @@ static hipError_t mlp_t(const np_shape& s, int layer, const void* x, const void*
   // at most one workgroup per CU (256), as many rounds of R rows per team
   // as they need, and the fewest workgroups that still finish in that many
   // rounds: fewer, fuller workgroups leave fewer partial sums, and about 200
-  // already draw the full HBM rate (us per call, 7B, k = 1651, two 4-row
-  // rounds: 207 workgroups 12.2, 236 12.4, 256 12.5).  So above 208 another
-  // round is added while 180 are left (70B, k = 2867: 180 workgroups 29.7, 239
-  // 30.7, 256 31.3; SwiGLU, 4670 rows: 195 23.1, 234 23.5; 7B dense: 197 43.4,
-  // 256 45.1; below 180: 7B, 165 12.9; d 3000 f32, k = 2500, 157 22.4, 209 20.5)
+  // already draw the full HBM rate (us per call, 7B, two 4-row rounds: k =
+  // 1651, 207 workgroups 12.3, 256 12.6; k = 2040, 255 and 256 14.0).  Above
+  // 208 another round is added while 180 are left: 239 or more in three
+  // rounds, 210 or more in seven.  Both sides of that line, us with one round
+  // less and one more: d 8192 bf16, k = 2863, 239 | 179 workgroups 29.7 | 29.0;
+  // d 4096 f16, k = 2850 16.9 | 16.5; d 5120 f16 20.0 | 19.9; d 4096 f32 27.3 |
+  // 26.8; but d 2048 f16 11.0 | 11.2 and d 3000 f32 21.0 | 21.6: up to 2% is
+  // left on wide rows just below 180, and narrow rows lose as much.  Far
+  // below, every width loses: k = 2500, 209 | 157, d 4096 f16 15.3 | 15.5, d
+  // 5120 18.1 | 18.7, d 3000 f32 19.1 | 20.5; and at or below 208 too: k =
+  // 1672, 209 | 140 12.4 | 12.6
   const int per = R * teams;
   int rounds = std::max(1, (n_active + per * 256 - 1) / (per * 256));
   auto wgs = [&](int r) { return (n_active + per * r - 1) / (per * r); };
@@ -861,8 +866,7 @@ static hipError_t mlp_t(const np_shape& s, int layer, const void* x, const void*
   bool fused = false;
   if (cpl == 1) {
     if (R == 4) launch_rows<T, 1, 4>(a, lds, lds_fused, want_fused, &fused, stream);
-    else if (R == 2) launch_rows<T, 1, 2>(a, lds, lds_fused, want_fused, &fused, stream);
-    else launch_rows<T, 1, 8>(a, lds, lds_fused, want_fused, &fused, stream);
+    else launch_rows<T, 1, 2>(a, lds, lds_fused, want_fused, &fused, stream);
   } else {
     if (R == 4) launch_rows<T, 2, 4>(a, lds, lds_fused, want_fused, &fused, stream);
     else launch_rows<T, 2, 2>(a, lds, lds_fused, want_fused, &fused, stream);

@@ -7,8 +7,6 @@
 // victims).
 #include <stdlib.h>
 
-#include <type_traits>
-
 #include "np_device.hpp"
 
 namespace np {
@@ -526,11 +524,9 @@ __device__ inline void select_hinted(const uint32_t (&key)[1][S::KPT], uint32_t 
       eq_all = (uint32_t)__builtin_amdgcn_readlane((int)eq, at);
     }
   }
-  if (!use) {
-    __syncthreads();  // every wave is done with the window's histogram
+  if (!use)  // in LDS of its own: slower waves may still read the window's
     kth = block_find_kth<S::NT, 1>(key, kk, &eq_take, work, work + 4096,
                                    work + 4096 + 3 * S::NW + 1);
-  }
   if (use && eq_take == eq_all) {  // every equal key is taken (usually the one)
     store_rows<KPT>(s.amask, [&](int r) { return key[0][r] >= kth; });
     lds_barrier();
@@ -693,7 +689,6 @@ __device__ inline bool delta_fast(int l, int32_t token, int na, const int (&qv)[
       take = m - (at > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)ages, at > 0 ? at - 1 : 0) : 0u);
       kth = mx - (uint32_t)at;
     } else {
-      __syncthreads();
       kth = block_find_kth<NT, 1>(key, m, &take, work, work + 4096, work + 4096 + 3 * S::NW + 1);
     }
     // all older ones and the first `take` equal ones in id order; one prefix
@@ -723,11 +718,12 @@ __device__ inline bool delta_fast(int l, int32_t token, int na, const int (&qv)[
     lds_barrier();
   }
   // 4. the slot pool in ascending order: its first nI slots go to the
-  //    incoming rows (ascending ids); 8 to 32 slots a thread
+  //    incoming rows (ascending ids); 8 or 16 slots a thread
   {
-    const int per = C <= 8 * NT ? 8 : (C <= 16 * NT ? 16 : 32);
+    static_assert(CPT <= 16, "NT threads of 16 slots cover the layer");
+    const int per = C <= 8 * NT ? 8 : 16;
     uint32_t bits = per * tid < C ? (s.smask[(per * tid) >> 5] >> ((per * tid) & 31)) : 0u;
-    if (per < 32) bits &= (1u << per) - 1u;
+    bits &= (1u << per) - 1u;
     uint32_t st;
     uint32_t pos = block_excl_scan_once<NT>(__builtin_popcount(bits), s.scan[3], &st);
     while (bits && pos < nI) {

@@ -74,6 +74,40 @@ def test_mlp_rounds_exact(d, dt, rows, wg, monkeypatch):
     assert B.np_device_error(bufs.ws) == B.NP_DEVERR_NOT_RESIDENT
 
 
+# (d, type, rows, NP_MLP_R, NP_MLP_TEAMS): forced rounds and teams that the
+# rule does not take by itself
+KNOBS = [
+    (256, "f32", 700, 2, 4), (264, "f16", 300, 4, 4), (1000, "bf16", 1030, 2, 4),
+    (2048, "f16", 515, 4, 2), (4096, "f16", 1030, 2, 2), (5120, "f16", 523, 2, 2),
+    (5120, "bf16", 2051, 4, 1), (8192, "bf16", 259, 4, 2),
+]
+
+
+@pytest.mark.parametrize("d,dt,n,R,teams", KNOBS, ids=[f"d{c[0]}_{c[1]}_R{c[3]}_T{c[4]}" for c in KNOBS])
+def test_mlp_forced_rounds_and_teams_exact(d, dt, n, R, teams, monkeypatch):
+    monkeypatch.setenv("NP_MLP_R", str(R))
+    monkeypatch.setenv("NP_MLP_TEAMS", str(teams))
+    F, C = n + 40, n + 20
+    cfg = W.Config("forced", 1, d, F, 8, n / F, C / F, dt, dt, 1, rho_given=0.0, k_override=n,
+                   c_override=C, dyadic=True, dyadic_w_range=1, dyadic_h_range=1)
+    say(f"[mlp forced] d {d} {dt} rows {n} R {R} teams {teams}")
+    bufs = Bufs(cfg)
+    bufs.reset()
+    rng = np.random.default_rng(d + n)
+    store, h = W.storage(cfg), W.hidden(cfg, 1)[0]
+    neuron = rng.permutation(F)[:C].astype(np.int32)
+    slots = rng.permutation(C)[:n].astype(np.int32)
+    rec, xv = orc.decode(dt, store[0][neuron[slots]]), orc.decode(dt, h)
+    a = np.maximum(rec[:, :d] @ xv, 0) * (rec[:, d:2 * d] @ xv)
+    assert np.max(np.abs(a)) < 2.0 ** 12 and np.max(np.abs(a) @ np.abs(rec[:, 2 * d:])) < 2.0 ** 6
+    y = torch.zeros(d * W.ITEMSIZE[dt], dtype=torch.uint8, device=DEV)
+    B.np_sparse_mlp(bufs.shape, 0, to_dev(h), to_dev(store[0][neuron]), to_dev(slots), n, y, bufs.ws)
+    torch.cuda.synchronize()
+    ref = orc.sparse_mlp(cfg, 0, h, store, neuron[slots])
+    assert np.array_equal(decode_y(orc, dt, y.cpu().numpy()), decode_y(orc, dt, ref))
+    assert B.np_device_error(bufs.ws) == 0
+
+
 def chains_of_256(a, down):
     """sum_j a[j] down[j] in fp32 as 256 workgroups sum it row by row (one fused
     multiply-add a row), their sums met in the reduce kernel's order."""
