@@ -356,9 +356,13 @@ __device__ inline void delta_layer(int l, int32_t token, const int32_t* A, int n
 // instead of a workgroup scan, masks built with ballots from the values that
 // are loaded anyway instead of LDS atomics, and the consistency of the slot map
 // checked once, which frees every later step of its checks: an inconsistent
-// layer takes delta_checked.  7B, per token: 23.3 us with 512
-// threads of 32 ids and about 45 barriers; 70B: 22.3 + 21.2 us in two kernels
-// that read the state from memory.  Now: 7B 11.3 us (13.5 a call), 70B 22 (32 a call).
+// layer takes delta_checked.  Per token before: 7B 23.3 us with 512 threads of
+// 32 ids and about 45 barriers; 70B 22.3 + 21.2 us in two kernels that read the
+// state from memory.  Now, a call: 7B 12.8 us, 70B 26.0 (kernel trace 12.4 and
+// 26.0).  A layer that has no hint yet or misses its window runs the full
+// search, and the call waits for its slowest layer: the first token takes 20.8
+// and 43.8 us, a token with a miss 19 and 34 to 38 (7B: one of 31; 70B, 79
+// layers: three of 11).
 // ---------------------------------------------------------------------------
 constexpr int SD_MAX_F = 32768;
 constexpr int SD_MAX_C = 16384;
