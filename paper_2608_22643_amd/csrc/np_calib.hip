@@ -28,7 +28,8 @@ namespace np {
 // tokens, wave (i, j) of its WGM x WGN waves MT x NT tiles of it (gate and up
 // of the same neurons, so that the activation needs no exchange).  The rows
 // stream through LDS in pieces of ROWB bytes, double buffered (row pitch
-// ROWB + 16 bytes: a fragment read touches every bank once).  In each
+// ROWB + 16 bytes: the 16 rows of a fragment start 4 banks apart; bank
+// conflicts are still a third of the LDS cycles).  In each
 // iteration a thread writes the pieces it holds in registers to the other
 // buffer, refills the registers from memory halfway through the products of
 // the current buffer, and one barrier, for LDS only, ends the iteration: a
