@@ -90,6 +90,10 @@ constexpr uint32_t MLP_SPIN_LIMIT = 1u << 20;
 // LDS; the launcher gives at least n / MLP_WG_ROWS workgroups: 128 at most).
 constexpr int MLP_WG_ROWS = 512;
 
+// The type in which the partial sums of y meet (the reduce kernel says why).
+template <class T>
+using RedSum = std::conditional_t<T::dtype == NP_F32, double, float>;
+
 template <class T>
 __device__ inline void store_y4(void* y, int col, float4 v) {
   if constexpr (T::dtype == NP_F32) {
@@ -136,19 +140,24 @@ __device__ inline void grid_barrier(void* ws, int n_wg, int gen0) {
 }
 
 // Grid barrier, then the column reduction of this workgroup's blocks.  Every
-// thread of the workgroup calls it; thread 0 holds `gen0`.  red: blockDim.x
-// float4 of LDS.
+// thread of the workgroup calls it; thread 0 holds `gen0`.  lds: blockDim.x
+// float4.
 template <class T>
-__device__ inline void fused_reduce(const MlpArgs& a, int gen0, float4* red) {
+__device__ inline void fused_reduce(const MlpArgs& a, int gen0, float4* lds) {
+  using A = RedSum<T>;
   grid_barrier(a.ws, a.n_wg, gen0);
   const int d = a.NV * T::V, nblk = (d + 15) / 16;
   const int t = threadIdx.x, nt = blockDim.x, lane = t & (WAVE - 1), w = t / WAVE;
   const int q = t & 3, rs = t >> 2, rstep = nt >> 2, nw = nt / WAVE;
+  struct alignas(16) Sums {
+    A v[4];
+  };
+  Sums* red = (Sums*)lds;  // wave, piece
   const __amdgpu_buffer_rsrc_t prs = make_rsrc(a.partials, (uint32_t)a.n_wg * nblk * 64u);
   for (int cb = blockIdx.x; cb < nblk; cb += a.n_wg) {
     const int col = cb * 16 + 4 * q;
     const bool cok = col < d;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    A acc[4] = {};
     for (int r0 = rs; r0 < a.n_wg; r0 += 4 * rstep) {  // rows in a fixed order
       float4 v[4];
 #pragma unroll
@@ -161,24 +170,25 @@ __device__ inline void fused_reduce(const MlpArgs& a, int gen0, float4* red) {
       }
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
-        acc.x += v[h].x;
-        acc.y += v[h].y;
-        acc.z += v[h].z;
-        acc.w += v[h].w;
+        acc[0] += v[h].x;
+        acc[1] += v[h].y;
+        acc[2] += v[h].z;
+        acc[3] += v[h].w;
       }
     }
-    acc = make_float4(sum_quads(acc.x), sum_quads(acc.y), sum_quads(acc.z), sum_quads(acc.w));
-    if (lane < 4) red[w * 4 + lane] = acc;
+    Sums s;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s.v[e] = sum_quads(acc[e]);
+    if (lane < 4) red[w * 4 + lane] = s;
     __syncthreads();
     if (t < 4 && cok) {  // waves in order
-      float4 o = red[t];
+      s = red[t];
       for (int k = 1; k < nw; ++k) {
-        o.x += red[k * 4 + t].x;
-        o.y += red[k * 4 + t].y;
-        o.z += red[k * 4 + t].z;
-        o.w += red[k * 4 + t].w;
+        const Sums o = red[k * 4 + t];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s.v[e] += o.v[e];
       }
-      store_y4<T>(a.y, col, o);
+      store_y4<T>(a.y, col, make_float4((float)s.v[0], (float)s.v[1], (float)s.v[2], (float)s.v[3]));
     }
     __syncthreads();  // red is reused by the next block
   }
@@ -497,7 +507,7 @@ constexpr int RED_COLS = 16;
 template <class T>
 __global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict__ partials,
                                                          int n_wg, int d, void* y) {
-  using A = std::conditional_t<T::dtype == NP_F32, double, float>;
+  using A = RedSum<T>;
   // thread t reads 16-byte piece q = t % 4 of partial rows t / 4, t / 4 + 64,
   // ...: each wave instruction reads 1 KiB of contiguous memory
   __shared__ A red[4][RED_COLS];  // wave, column

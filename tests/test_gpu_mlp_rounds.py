@@ -128,8 +128,9 @@ def chains_of_256(a, down):
     return y.astype(np.float64)
 
 
+@pytest.mark.parametrize("fused", ["0", "1"], ids=["two_kernels", "fused"])
 @pytest.mark.parametrize("dense", [True, False], ids=["dense", "sparse"])
-def test_mlp_fp32_sums_no_worse_than_256_chains(dense):
+def test_mlp_fp32_sums_no_worse_than_256_chains(dense, fused, monkeypatch):
     """In fp32 the down projection of a long range is no further from the exact
     sum than 256 plain chains of rows would be, although fewer workgroups run:
     every g is 1 and every u has 8 bits, so the activations are exact and the
@@ -137,7 +138,8 @@ def test_mlp_fp32_sums_no_worse_than_256_chains(dense):
     chains of 24 that 256 workgroups have are 1.16e-7 off, chains of 32 rows
     1.28e-7 (dense), sums by rounds of 4 that meet in fp64 0.75e-7."""
     d, F = 1024, 6000
-    say(f"[mlp fp32 sums] dense {dense}")
+    monkeypatch.setenv("NP_MLP_FUSED", fused)
+    say(f"[mlp fp32 sums] dense {dense} fused {fused}")
     rng = np.random.default_rng(3)
     a = (rng.integers(1, 256, F) * rng.choice([-1, 1], F)).astype(np.float32) / 64
     rec = np.zeros((F, 3 * d), np.float32)
